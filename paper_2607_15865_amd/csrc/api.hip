@@ -427,7 +427,7 @@ PrefillWs plan_prefill(const layer_s* L, int T, int hist) {
     w.g = cv.take((size_t)T * L->F_pad * 2);
     // split-K partials of each GEMM and the attention chunk states, used one kernel at a time
     w.part = cv.take(std::max({w.qkv.part_bytes, w.o.part_bytes, w.gu.part_bytes, w.down.part_bytes, w.at.part_bound}));
-    w.cnt = cv.take((size_t)kGemmCounters * 8);   // tagged split-K arrival counters
+    w.cnt = cv.take((size_t)4 * kGemmCounters * 4);   // split-K arrival counters, one set per GEMM
     w.total = cv.off;
     return w;
 }
@@ -829,13 +829,13 @@ int run_prefill(layer_s* L, const float* x, const int32_t* pos, int T, int hist,
     f16* xn2 = (f16*)(base + w.xn2);
     f16* g = (f16*)(base + w.g);
     float* part = (float*)(base + w.part);
-    unsigned long long* cnt = (unsigned long long*)(base + w.cnt);
+    unsigned* cnt = (unsigned*)(base + w.cnt);
     const int H = c.hidden, d = c.head_dim, qd = c.n_heads * d;
     for (const GemmPlan* gp : {&w.qkv, &w.o, &w.gu, &w.down})
         if (gp->S > 1 && gp->tiles > kGemmCounters) return fail(W4_EUNSUPPORTED, "split-K tile count above %d", kGemmCounters);
 
     int rc = 0;
-    { ProfScope ps(L, stage, 0, st); rc |= launch_rmsnorm(x, (const uint16_t*)L->attn_norm.p, c.rms_eps, T, H, xn1, L->err, st); }
+    { ProfScope ps(L, stage, 0, st); rc |= launch_rmsnorm(x, (const uint16_t*)L->attn_norm.p, c.rms_eps, T, H, xn1, L->err, st, cnt, 4 * kGemmCounters); }
     EpiArgs e = base_epi(L);
     e.q_out = q;
     e.k_cache = (uint16_t*)kc;
@@ -844,7 +844,7 @@ int run_prefill(layer_s* L, const float* x, const int32_t* pos, int T, int hist,
     e.cache_stride_h = (long long)c.max_seq * d;
     e.pos = pos;
     e.slot_base = hist;
-    { ProfScope ps(L, stage, 1, st); rc |= launch_gemm_w4(EPI_QKV, xn1, H, L->qkv.d, e, w.qkv, T, part, cnt, next_epoch(), st); }
+    { ProfScope ps(L, stage, 1, st); rc |= launch_gemm_w4(EPI_QKV, xn1, H, L->qkv.d, e, w.qkv, T, part, cnt, st); }
     AttnPrefillArgs aa{};
     aa.q = q;
     aa.k_cache = (const uint16_t*)kc;
@@ -863,15 +863,15 @@ int run_prefill(layer_s* L, const float* x, const int32_t* pos, int T, int hist,
     EpiArgs eo = base_epi(L);
     eo.resid = x;
     eo.out_f32 = h;
-    { ProfScope ps(L, stage, 3, st); rc |= launch_gemm_w4(EPI_RESID, attn, qd, L->o.d, eo, w.o, T, part, cnt, next_epoch(), st); }
+    { ProfScope ps(L, stage, 3, st); rc |= launch_gemm_w4(EPI_RESID, attn, qd, L->o.d, eo, w.o, T, part, cnt + kGemmCounters, st); }
     { ProfScope ps(L, stage, 4, st); rc |= launch_rmsnorm(h, (const uint16_t*)L->mlp_norm.p, c.rms_eps, T, H, xn2, L->err, st); }
     EpiArgs eg = base_epi(L);
     eg.act_out = g;
-    { ProfScope ps(L, stage, 5, st); rc |= launch_gemm_w4(EPI_SWIGLU, xn2, H, L->gu.d, eg, w.gu, T, part, cnt, next_epoch(), st); }
+    { ProfScope ps(L, stage, 5, st); rc |= launch_gemm_w4(EPI_SWIGLU, xn2, H, L->gu.d, eg, w.gu, T, part, cnt + 2 * kGemmCounters, st); }
     EpiArgs ed = base_epi(L);
     ed.resid = h;
     ed.out_f32 = y;
-    { ProfScope ps(L, stage, 6, st); rc |= launch_gemm_w4(EPI_RESID, g, L->F_pad, L->down.d, ed, w.down, T, part, cnt, next_epoch(), st); }
+    { ProfScope ps(L, stage, 6, st); rc |= launch_gemm_w4(EPI_RESID, g, L->F_pad, L->down.d, ed, w.down, T, part, cnt + 3 * kGemmCounters, st); }
     if (rc) return fail(W4_EHIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError()));
     return W4_OK;
 }

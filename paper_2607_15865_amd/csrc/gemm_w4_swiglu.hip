@@ -1,0 +1,8 @@
+// Prefill GEMM (gemm_w4.h), SwiGLU epilogue.  One source per epilogue: the
+// kernel's variants compile in parallel.
+#include "gemm_w4.h"
+
+int launch_gemm_w4_swiglu(const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmPlan& p, const GemmShape& gs,
+                      hipStream_t stream) {
+    return launch_epi<EPI_SWIGLU>(p, X, ldx, W, ep, gs, stream);
+}

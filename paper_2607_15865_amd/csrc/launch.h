@@ -42,18 +42,34 @@ __device__ __forceinline__ void epi_qkv_pair(const EpiArgs& ep, int row, int n_b
     }
 }
 
-// Prefill GEMM launch plan: row tile (32 * TM rows), k splits S, grid.
+// Prefill GEMM launch plan: row tile (32 * TM rows), block shape (WN waves
+// side by side, 64 columns each; KG groups of them that share out the block's
+// k range), k splits S, grid.
 struct GemmPlan {
-    int TM = 4, S = 1, nrb = 0, ncb = 0, tiles = 0;
+    int TM = 4, WN = 4, KG = 1, S = 1, nrb = 0, ncb = 0, tiles = 0;
     size_t part_bytes = 0;        // fp32 partial sums (S > 1)
 };
 GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus);
-// part: plan.part_bytes of workspace; cnt: plan.tiles 64-bit arrival
-// counters in any state; tag: non-zero, different from the tag of every
-// earlier launch that used the same counters.  part and cnt are unused when
-// plan.S == 1.
+// part: plan.part_bytes of workspace; cnt: plan.tiles arrival counters, zeroed
+// by an earlier launch on the stream (launch_rmsnorm) and used by this launch
+// alone.  Both are unused when plan.S == 1.
 int launch_gemm_w4(int epi, const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmPlan& plan,
-                   int M, float* part, unsigned long long* cnt, unsigned tag, hipStream_t stream);
+                   int M, void* part, unsigned* cnt, hipStream_t stream);
+
+// (the kernel's launchers, one source per epilogue)
+struct GemmShape {
+    int M, nrb, ncb, S, KB;
+    unsigned long long* part;    // [nrb * ncb][S][TM * 16][WN][64] partial pairs (S > 1)
+    unsigned* cnt;               // [nrb * ncb] arrival counters, zeroed by an earlier launch (S > 1)
+    int rows;                    // blocks in row order (else in column order)
+};
+
+int launch_gemm_w4_qkv(const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmPlan& plan,
+                       const GemmShape& gs, hipStream_t stream);
+int launch_gemm_w4_resid(const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmPlan& plan,
+                         const GemmShape& gs, hipStream_t stream);
+int launch_gemm_w4_swiglu(const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmPlan& plan,
+                          const GemmShape& gs, hipStream_t stream);
 
 struct GemvArgs {
     DevLinear W;
@@ -71,8 +87,10 @@ struct GemvArgs {
 };
 int launch_gemv_w4(int epi, bool norm, const GemvArgs& a, hipStream_t stream);
 
+// zero, nzero: words that the launch also sets to zero (arrival counters of
+// later launches), or null
 int launch_rmsnorm(const float* x, const uint16_t* gamma, float eps, int M, int H, f16* out, int* err,
-                   hipStream_t stream);
+                   hipStream_t stream, unsigned* zero = nullptr, int nzero = 0);
 
 struct AttnPrefillArgs {
     const uint16_t* q;       // bf16 [T][nq][d]

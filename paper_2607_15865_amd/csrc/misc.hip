@@ -11,9 +11,10 @@ namespace {
 template <int NV>
 __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ x, const uint16_t* __restrict__ gamma,
                                                       float eps, int H, f16* __restrict__ out,
-                                                      int* __restrict__ err) {
+                                                      int* __restrict__ err, unsigned* __restrict__ zero, int nzero) {
     __shared__ float part[4];
     const int row = blockIdx.x, tid = threadIdx.x;
+    for (int i = row * 256 + tid; i < nzero; i += gridDim.x * 256) zero[i] = 0u;
     const float* xr = x + (size_t)row * H;
     float4 v[NV];
     uint2 g[NV];
@@ -110,14 +111,14 @@ __global__ void debug_dequant_kernel(DevLinear W, const int32_t* __restrict__ co
 }  // namespace
 
 int launch_rmsnorm(const float* x, const uint16_t* gamma, float eps, int M, int H, f16* out, int* err,
-                   hipStream_t stream) {
+                   hipStream_t stream, unsigned* zero, int nzero) {
     if (H % 4 || H > 16 * 1024) return -1;
     const int nv = (H + 1023) / 1024;
-    if (nv <= 1) hipLaunchKernelGGL(rmsnorm_kernel<1>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err);
-    else if (nv <= 2) hipLaunchKernelGGL(rmsnorm_kernel<2>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err);
-    else if (nv <= 4) hipLaunchKernelGGL(rmsnorm_kernel<4>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err);
-    else if (nv <= 8) hipLaunchKernelGGL(rmsnorm_kernel<8>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err);
-    else hipLaunchKernelGGL(rmsnorm_kernel<16>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err);
+    if (nv <= 1) hipLaunchKernelGGL(rmsnorm_kernel<1>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err, zero, nzero);
+    else if (nv <= 2) hipLaunchKernelGGL(rmsnorm_kernel<2>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err, zero, nzero);
+    else if (nv <= 4) hipLaunchKernelGGL(rmsnorm_kernel<4>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err, zero, nzero);
+    else if (nv <= 8) hipLaunchKernelGGL(rmsnorm_kernel<8>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err, zero, nzero);
+    else hipLaunchKernelGGL(rmsnorm_kernel<16>, dim3(M), dim3(256), 0, stream, x, gamma, eps, H, out, err, zero, nzero);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

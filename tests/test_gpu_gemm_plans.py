@@ -1,0 +1,57 @@
+"""The prefill GEMM's block shapes and splits against the CPU oracle, at the
+sizes where they can go wrong: rows around the row tiles of 32, 64 and 128, k
+ranges with fewer iterations than k groups (hidden 256), with odd remainders
+over the k groups and splits (hidden 896 and 1152, FFN 688 and 4736), more rows
+than columns (blocks in row order), and every weight format.  The bound is the
+parity bar of all stage tests."""
+import functools
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import layer as O
+from paper_2607_15865_amd import binding, synth
+from gpu_helpers import assert_parity, bits_to_torch_f32, cache_values, log
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "h256": synth.CONFIGS["tiny"],
+    "h896": synth.replace(synth.CONFIGS["qwen05b"], ffn=4736, max_seq=512),
+    "h1152": synth.LayerConfig("h1152", 1152, 9, 3, 128, 1024, 128, 1e-6, 1e4, 512, 8, 7),
+}
+FORMATS = {"int4": {}, "zeros": dict(with_zeros=True), "int8": dict(fmt="int8"), "bf16": dict(fmt="bf16")}
+CASES = ([("h256", "int4", T) for T in (9, 32, 33, 65, 127)] +
+         [("h896", f, T) for f, Ts in (("int4", (31, 64, 129, 300)), ("zeros", (33, 200)), ("int8", (65,)), ("bf16", (64, 97))) for T in Ts] +
+         [("h1152", f, T) for f, Ts in (("int4", (9, 96, 257)), ("zeros", (64,)), ("int8", (10, 130)), ("bf16", (33,))) for T in Ts])
+
+
+@functools.lru_cache(maxsize=1)
+def layer(shape, fmt):
+    cfg = SHAPES[shape]
+    w = synth.make_layer(cfg, 0, **FORMATS[fmt])
+    return cfg, w, O.dequant_layer(w, cfg), binding.Layer(cfg, w)
+
+
+@pytest.mark.parametrize("shape,fmt,T", CASES)
+def test_prefill_gemm_plan(shape, fmt, T):
+    cfg, w, W, lay = layer(shape, fmt)
+    log(f"prefill {shape} {fmt} T={T}")
+    lay.set_decode_path(1)                       # the prefill kernels for every T
+    bits = synth.activations(cfg, synth.TID_X_PREFILL, T)
+    x = bits_to_torch_f32(bits)
+    k, v = lay.new_cache(1, 0)
+    outs = []
+    for _ in range(2):                           # a second call finds the first one's counters and partial sums
+        y = torch.full_like(x, float("nan"))
+        lay.prefill(x, torch.arange(T, dtype=torch.int32, device="cuda"), k, v, y)
+        torch.cuda.synchronize()
+        outs.append(y)
+    assert lay.error() == 0
+    assert torch.equal(outs[0], outs[1]), "the k groups and splits add in a fixed order"
+    yo, ko, vo = O.prefill(w, cfg, O.bf16_to_f64(bits), np.arange(T), W=W)
+    assert_parity(outs[0].cpu().numpy(), yo, "y")
+    assert_parity(cache_values(k)[0][:, :T].transpose(1, 0, 2), ko, "new K")
+    assert_parity(cache_values(v)[0][:, :T].transpose(1, 0, 2), vo, "new V")
+    assert not np.any(cache_values(k)[0][:, T:]), "slots past the prompt are untouched"
