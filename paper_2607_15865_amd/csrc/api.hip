@@ -432,20 +432,19 @@ PrefillWs plan_prefill(const layer_s* L, int T, int hist) {
     return w;
 }
 
-// keys per chunk of the separate-kernel decode attention (its split kernel
-// stages one chunk of K and V in LDS)
-int decode_chunk(int) { return 64; }
-
-struct DecodeWs { size_t q, part, attn, h, g, xn, total; int chunk, nchunks; };
+struct DecodeWs { size_t q, part, attn, h, g, xn, total; int nsplit; };
 DecodeWs plan_decode(const layer_s* L, int B, int max_ctx) {
     const layer_config& c = L->cfg;
     const size_t qd = (size_t)c.n_heads * c.head_dim;
     DecodeWs w;
-    w.chunk = decode_chunk(max_ctx);
-    w.nchunks = (max_ctx + 1 + w.chunk - 1) / w.chunk;
+    // attention shares; their arrival counters live in g, which is written
+    // only after the attention (a layer whose g is too small takes one share)
+    w.nsplit = c.n_kv_heads * 4 <= L->F_pad * 2 ? attn_decode_splits(B, c.n_kv_heads, max_ctx, L->num_cus) : 1;
+    // (sized for a share per 64 keys, at least as many as there are)
+    const int nchunks = (max_ctx + 64) / 64;
     Carve cv;
     w.q = cv.take((size_t)B * qd * 2);
-    w.part = cv.take((size_t)B * c.n_heads * w.nchunks * (c.head_dim + 2) * 4);
+    w.part = cv.take((size_t)B * c.n_heads * nchunks * (c.head_dim + 2) * 4);
     w.attn = cv.take((size_t)B * qd * 2);
     w.h = cv.take((size_t)B * c.hidden * 4);
     w.g = cv.take((size_t)B * L->F_pad * 2);
@@ -566,14 +565,6 @@ uint32_t next_epoch() {
     return e;
 }
 
-int gemv_ksplit(const DevLinear& W, int want_blocks, int B) {
-    const int pairs = W.N_dev / 64, KB = W.K_pad / 64;
-    int ks = std::max(1, std::min(KB, (want_blocks + pairs - 1) / pairs));
-    // activation slice of B rows must fit the LDS budget (128 KB)
-    while ((long long)B * ((KB + ks - 1) / ks) * 64 * 2 > 128 * 1024 && ks < KB) ks++;
-    return ks;
-}
-
 // Event pair around kernel `k` of `stage` when it is the profiled one.
 struct ProfScope {
     layer_s* L;
@@ -670,11 +661,12 @@ int launch_fused(layer_s* L, const FusedPlan& fp, const float* x, const int32_t*
 // attention, chunk merge).  shared: the B rows are consecutive tokens of one
 // sequence with one cache (prefill / prefill_kv of at most 8 tokens), row b
 // at context ctx_base + b: the q/k/v GEMV writes every row's new key and
-// value before the attention kernel reads the cache.  ps_stage: the profiling
-// stage the launches count for (2 decode, 0/1 prefill).
+// value before the attention kernel reads the cache.  ordered: the result does
+// not depend on timing (gemv_resid_plan).  ps_stage: the profiling stage the
+// launches count for (2 decode, 0/1 prefill).
 int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t* ctx_lens, int ctx_base, bool shared,
                    const float* attn_mask, int B, int max_ctx, void* kc, void* vc, float* y, void* ws,
-                   size_t ws_bytes, hipStream_t st, int ps_stage) {
+                   size_t ws_bytes, hipStream_t st, int ps_stage, bool ordered) {
     const layer_config& c = L->cfg;
     const DecodeWs w = plan_decode(L, B, max_ctx);
     if (ws_bytes < w.total) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, w.total);
@@ -695,6 +687,7 @@ int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t
     a1.eps = c.rms_eps;
     a1.B = B;
     a1.ksplit = 1;
+    a1.num_cus = L->num_cus;
     a1.ep = base_epi(L);
     a1.ep.q_out = q;
     a1.ep.k_cache = (uint16_t*)kc;
@@ -704,11 +697,19 @@ int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t
     a1.ep.pos = pos;
     a1.ep.slot_dev = shared ? nullptr : ctx_lens;
     a1.ep.slot_base = ctx_base;
-    a1.copy_src = x;
-    a1.copy_dst = h;
-    a1.copy_n = B * H;
-    // with 4 rows or more the rows are normalised once, not in every block
-    const bool prenorm = B >= 4;
+    GemvArgs a2{}, a4{};                    // o_proj and down: h = x + A Wo, y = h + g Wd
+    a2.W = L->o.d;
+    a4.W = L->down.d;
+    a2.B = a4.B = B;
+    a2.num_cus = a4.num_cus = L->num_cus;
+    gemv_resid_plan(a2, ordered);
+    gemv_resid_plan(a4, ordered);
+    a1.clear = h;
+    a1.nclear = a2.ksplit > 1 ? B * H : 0;
+    a1.zero = (unsigned*)g;                 // the attention's arrival counters
+    a1.nzero = w.nsplit > 1 ? B * c.n_kv_heads : 0;
+    // the rows are normalised in every block, or, many of them, once beforehand
+    const bool prenorm = !gemv_norm_fits(B, H);
     f16* xn = (f16*)(base + w.xn);
     if (prenorm) {
         rc |= launch_rmsnorm(x, (const uint16_t*)L->attn_norm.p, c.rms_eps, B, H, xn, L->err, st);
@@ -733,19 +734,16 @@ int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t
     ad.nq = c.n_heads;
     ad.nkv = c.n_kv_heads;
     ad.d = d;
-    ad.chunk = w.chunk;
-    ad.nchunks = w.nchunks;
+    ad.nsplit = w.nsplit;
+    ad.cnt = (unsigned*)g;
     ad.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d));
     ad.err = L->err;
     { ProfScope ps(L, ps_stage, ps_stage == 2 ? 1 : 2, st); rc |= launch_attn_decode(ad, st); }
 
-    GemvArgs a2{};
-    a2.W = L->o.d;
     a2.x_f16 = attn;
     a2.ldx = qd;
-    a2.B = B;
-    a2.ksplit = gemv_ksplit(L->o.d, 512, B);
     a2.ep = base_epi(L);
+    a2.ep.resid = x;
     a2.ep.out_f32 = h;
     { ProfScope ps(L, ps_stage, 3, st); rc |= launch_gemv_w4(EPI_RESID, false, a2, st); }
 
@@ -756,11 +754,11 @@ int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t
     a3.eps = c.rms_eps;
     a3.B = B;
     a3.ksplit = 1;
+    a3.num_cus = L->num_cus;
     a3.ep = base_epi(L);
     a3.ep.act_out = g;
-    a3.copy_src = h;
-    a3.copy_dst = y;
-    a3.copy_n = B * H;
+    a3.clear = y;
+    a3.nclear = a4.ksplit > 1 ? B * H : 0;
     if (prenorm) {
         rc |= launch_rmsnorm(h, (const uint16_t*)L->mlp_norm.p, c.rms_eps, B, H, xn, L->err, st);
         a3.x_f16 = xn;
@@ -768,23 +766,34 @@ int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t
     }
     { ProfScope ps(L, ps_stage, ps_stage == 2 ? 4 : 5, st); rc |= launch_gemv_w4(EPI_SWIGLU, !prenorm, a3, st); }
 
-    GemvArgs a4{};
-    a4.W = L->down.d;
     a4.x_f16 = g;
     a4.ldx = L->F_pad;
-    a4.B = B;
-    a4.ksplit = gemv_ksplit(L->down.d, 512, B);
     a4.ep = base_epi(L);
+    a4.ep.resid = h;
     a4.ep.out_f32 = y;
     { ProfScope ps(L, ps_stage, ps_stage == 2 ? 5 : 6, st); rc |= launch_gemv_w4(EPI_RESID, false, a4, st); }
     if (rc) return fail(W4_EHIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError()));
     return W4_OK;
 }
 
+// With the automatic path, one or two rows go to the kernel sequence (in its
+// ordered form: the persistent launch's results do not depend on timing either)
+// where it is the faster one: two rows, and one row whose keys one block per
+// kv head walks on its own.  Persistent / sequence, us: Llama-8B, 1 row, 60
+// keys 45.6 / 43.5, 300 47.2 / 45.4, 600 47.2 / 48.5, 4000 47.7 / 50.1; 2 rows,
+// 300 52.3 / 46.8, 2000 58.6 / 49.7, 8000 83.3 / 56.6; Qwen-7B, 1 row, 300
+// 52.9 / 50.0, 8000 55.2 / 57.2; 2 rows, 2000 59.9 / 54.9; Qwen-0.5B, 1 row, 60
+// 31.6 / 29.5, 8000 33.3 / 38.2; 2 rows, 2000 36.7 / 34.8.  Layers narrower than
+// those (2 us apart) stay with the one launch.
+bool prefer_seq(const layer_s* L, int B, int max_ctx) {
+    return L->decode_path == 0 && L->cfg.hidden >= 512 && (B == 2 || max_ctx < 512);
+}
+
 // Prefill / prefill_kv of a few tokens runs on the decode kernels, the tokens
 // as rows sharing one cache: up to 2 tokens (4 with decode path 2) as one
-// persistent launch, up to 8 (decode path 0) as the decode kernel sequence;
-// decode path 1 keeps every call on the prefill kernels.
+// persistent launch or the decode kernel sequence (prefer_seq), up to 8 (decode
+// path 0) as the sequence; decode path 1 keeps every call on the prefill
+// kernels.
 FusedPlan small_prefill_plan(layer_s* L, int T, int hist) {
     if (!((L->decode_path == 0 && T <= 2) || (L->decode_path == 2 && T <= 4))) return FusedPlan{};
     return plan_fused(L, T, hist + T - 1, true);
@@ -795,7 +804,7 @@ size_t prefill_ws_bytes(layer_s* L, int T, int hist) {
     size_t n = plan_prefill(L, T, hist).total;
     const FusedPlan fp = small_prefill_plan(L, T, hist);
     if (fp.ok) n = std::max(n, fp.total);
-    else if (small_prefill_seq(L, T)) n = std::max(n, plan_decode(L, T, hist + T - 1).total);
+    if (small_prefill_seq(L, T)) n = std::max(n, plan_decode(L, T, hist + T - 1).total);
     return n;
 }
 
@@ -810,7 +819,8 @@ int run_prefill(layer_s* L, const float* x, const int32_t* pos, int T, int hist,
     hipStream_t st = (hipStream_t)stream_;
     const int stage = hist > 0 ? 1 : 0;
     const FusedPlan fp = small_prefill_plan(L, T, hist);
-    if (fp.ok) {
+    const bool seq = fp.ok && prefer_seq(L, T, hist + T - 1) && ws_bytes >= plan_decode(L, T, hist + T - 1).total;
+    if (fp.ok && !seq) {
         if (ws_bytes < fp.total) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, fp.total);
         int rc;
         { ProfScope ps(L, stage, 7, st); rc = launch_fused(L, fp, x, pos, nullptr, hist, true, nullptr, T, kc, vc, y, ws, st); }
@@ -818,7 +828,7 @@ int run_prefill(layer_s* L, const float* x, const int32_t* pos, int T, int hist,
         return W4_OK;
     }
     if (small_prefill_seq(L, T))
-        return run_decode_seq(L, x, pos, nullptr, hist, true, nullptr, T, hist + T - 1, kc, vc, y, ws, ws_bytes, st, stage);
+        return run_decode_seq(L, x, pos, nullptr, hist, true, nullptr, T, hist + T - 1, kc, vc, y, ws, ws_bytes, st, stage, seq);
     const PrefillWs w = plan_prefill(L, T, hist);
     if (ws_bytes < w.total) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, w.total);
     char* base = (char*)ws;
@@ -884,19 +894,20 @@ int decode_run(layer_s* L, const float* x, const int32_t* pos, const int32_t* ct
                const float* attn_mask, int B, void* kc, void* vc, float* y, void* ws, size_t ws_bytes,
                hipStream_t st, int ps_stage) {
     const FusedPlan fp = decode_fused_choice(L, B, max_ctx);
-    if (fp.ok) {
+    const bool seq = fp.ok && prefer_seq(L, B, max_ctx) && ws_bytes >= plan_decode(L, B, max_ctx).total;
+    if (fp.ok && !seq) {
         if (ws_bytes < fp.total) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, fp.total);
         int rc;
         { ProfScope ps(L, ps_stage, 6, st); rc = launch_fused(L, fp, x, pos, ctx_lens, 0, false, attn_mask, B, kc, vc, y, ws, st); }
         if (rc) return fail(W4_EHIP, "persistent decode launch failed: %s", hipGetErrorString(hipGetLastError()));
         return W4_OK;
     }
-    return run_decode_seq(L, x, pos, ctx_lens, 0, false, attn_mask, B, max_ctx, kc, vc, y, ws, ws_bytes, st, ps_stage);
+    return run_decode_seq(L, x, pos, ctx_lens, 0, false, attn_mask, B, max_ctx, kc, vc, y, ws, ws_bytes, st, ps_stage, seq);
 }
 
-// The persistent decode plan a decode call of B rows uses: forced by path 2,
-// automatic for at most 2 rows (from 3 rows on the kernel sequence is the
-// faster one); not ok means the kernel sequence.
+// The persistent decode plan a decode call of B rows may use: forced by path 2,
+// automatic for at most 2 rows (see also prefer_seq; from 3 rows on the kernel
+// sequence is the faster one); not ok means the kernel sequence.
 FusedPlan decode_fused_choice(layer_s* L, int B, int max_ctx) {
     if (L->decode_path == 1 || (L->decode_path == 0 && B > 2)) return FusedPlan{};
     return plan_fused(L, B, max_ctx, true);
@@ -1497,6 +1508,7 @@ int lm_head(lm_t M, const float* x, int32_t B, float* logits, int32_t* next_toke
         a.ldx = H;
         a.B = std::min(kLmRows, B - r0);
         a.ksplit = 1;
+        a.ct = 2;
         a.ep.resid = (const float*)M->zeros.p;
         a.ep.out_f32 = logits + (size_t)r0 * V;
         rc = launch_gemv_w4(EPI_RESID, false, a, st);

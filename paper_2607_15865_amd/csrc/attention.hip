@@ -32,11 +32,10 @@
 // kernel merges the chunks of each query tile in chunk order with the
 // log-sum-exp rule, so results do not depend on timing.
 //
-// Decode: one query per sequence.  Split-KV: a block stages one 64-key chunk
-// of one kv head's cache in LDS once for all the query heads of its group,
-// forms scores and P V on the 16x16x32 bf16 MFMA, writes a partial (max,
-// sum, unnormalised output), and a combine kernel merges the chunks with the
-// log-sum-exp rule.
+// Decode: one query per sequence.  Split-KV: a block walks a share of one kv
+// head's cache for all the query heads of its group (attn_decode_kernel); the
+// last block of a head group to finish merges the shares with the log-sum-exp
+// rule.
 #include "common.h"
 #include "launch.h"
 
@@ -310,99 +309,130 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_merge_kernel(AttnP
 
 // ---------------------------------------------------------------- decode
 
-constexpr int MAXR = 8;      // query heads per kv head
-constexpr int DEC_CH = 64;       // keys per chunk of the decode split kernel
+constexpr int MAXR = 8;          // query heads per kv head
+constexpr int DEC_W = 8;         // waves per block
+constexpr int DEC_ST = 32 * DEC_W;   // keys per stage of a block (32 per wave)
 
-// One chunk of DEC_CH keys of one (row, kv head) for all r query heads of
-// the group, on the 16x16x32 bf16 MFMA (the design of the persistent decode's
-// attention units): the chunk's K and V rows go straight from memory to LDS
-// (16-byte chunks XOR-swizzled by row), the heads are the MFMA columns
-// (padded to 16), and each of the two 32-key groups goes to two waves that
-// both form its scores S^T = K Q^T and softmax in registers and each take
-// half of the dims of O^T = V^T P^T (P as a bf16 pair hi + lo).  Rows past
-// the chunk's keys read the chunk's first row (a written cache slot, so V
-// stays finite) and get probability 0.  The two groups' states are merged
-// in LDS into the chunk partial (max, sum, unnormalised output).
+// One block: a contiguous share of the keys of one (row, kv head), all r query
+// heads of the group.  Bound by the cache read, so everything is arranged to
+// keep loads in flight: the eight waves take 32 keys each of every 256-key
+// stage on their own (no barrier in the loop), and a wave's K and V of the
+// next stage are on their way into registers while the current one is
+// computed.  K goes from memory straight into the MFMA's A operand; V passes
+// through LDS, where the transposing read forms V^T.  (With both staged in LDS
+// by direct-to-LDS loads, one 64-key chunk per block, a block had nothing in
+// flight while it computed, and every chunk cost a launch slot, a partial
+// state and its share of the merge.)
+//
+// Scores S^T = K Q^T and O^T = V^T P^T on the 16x16x32 bf16 MFMA: the heads
+// are the columns (padded to 16); the key rows are fed in the order that
+// leaves the probabilities in the operand layout of P^T; P is a bf16 pair
+// hi + lo.  Every wave keeps a running max, sum and output; the waves meet in
+// LDS at the end.  Rows past the share's keys read its first row (a written
+// cache slot, so V stays finite) and get probability 0.
+//
+// With more than one share the blocks store their states (device-coherent, as
+// the prefill GEMM's split sums) and count their arrival; the last one merges
+// the shares in order, so the result does not depend on timing.  One launch
+// instead of two: at these sizes a launch costs as much as the merge.  Whole
+// decode before / after this kernel and the GEMV's present form: Qwen-7B, 8 rows
+// of up to 8192 keys 121.9 / 86.6 us, Llama-8B, 4 rows of up to 1500 with a mask
+// 73.7 / 59.9; the attention alone at the former 39 / 27 us (105 MB of cache).
 template <int D>
-__global__ void __launch_bounds__(256) attn_decode_split_kernel(AttnDecodeArgs a) {
-    constexpr int NCK = D / 8, KROWS = 1024 / (2 * D), CH = DEC_CH;
+__global__ void __launch_bounds__(64 * DEC_W) attn_decode_kernel(AttnDecodeArgs a) {
+    constexpr int NCK = D / 8, KROWS = 1024 / (2 * D), NV = 32 / KROWS, NS = D / 32;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    unsigned char* Kst = smem;                                         // [CH][D] bf16
-    unsigned char* Vst = smem + CH * D * 2;                            // [CH][D] bf16
-    float* ored = reinterpret_cast<float*>(Vst + CH * D * 2);          // [2][MAXR][D]
-    float* gst = ored + 2 * MAXR * D;                                  // [2][MAXR][2]
-    float* mst = gst + 2 * MAXR * 2;                                   // [CH]
-    uint16_t* qb = reinterpret_cast<uint16_t*>(mst + CH);              // [MAXR][D]
-
+    __shared__ float gst[DEC_W][MAXR][2];
+    __shared__ unsigned last_flag;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.x / a.nkv, g = blockIdx.x % a.nkv;
-    const int chunk = blockIdx.y;
     const int ctx = a.ctx_lens ? a.ctx_lens[b] : a.ctx_base + b;
-    const int start = chunk * CH, end = min(start + CH, ctx + 1);
-    if (start >= end) return;
-    const int nkeys = end - start, ng = (nkeys + 31) / 32;
+    const int ns = (ctx + DEC_ST) / DEC_ST;                     // stages of ctx + 1 keys
+    const int n = min(a.nsplit, ns), part = blockIdx.y;
+    if (part >= n) return;
+    const int start = (int)((long long)part * ns / n) * DEC_ST;
+    const int end = min((int)((long long)(part + 1) * ns / n) * DEC_ST, ctx + 1);
     const int r = a.nq / a.nkv;
     const uint16_t* kc = a.k_cache + (size_t)b * a.stride_b + (size_t)g * a.stride_h;
     const uint16_t* vc = a.v_cache + (size_t)b * a.stride_b + (size_t)g * a.stride_h;
-    auto kswz = [](int k) { return ((k & 3) | ((k >> 1) & 12)) & (NCK - 1); };
+    const float LOG2E = 1.4426950408889634f;
+    const int n16 = lane & 15, q4 = lane >> 4;
+    unsigned char* const Vst = smem + wave * 32 * D * 2;        // this wave's [32 keys][D], chunks swizzled
     auto vswz = [](int k) { return 2 * ((k >> 3) & 3); };
 
-    // K, V rows (and the mask values) straight to LDS, q of the group's heads
-    for (int i = wave; i < CH / KROWS; i += 4) {
-        const int row = i * KROWS + lane / NCK, pc = lane % NCK;
-        const size_t src = (size_t)(start + (row < nkeys ? row : 0)) * D;
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(kc + src + (pc ^ kswz(row)) * 8),
-                                         (__attribute__((address_space(3))) void*)(Kst + i * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(vc + src + (pc ^ vswz(row)) * 8),
-                                         (__attribute__((address_space(3))) void*)(Vst + i * 1024), 16, 0, 0);
-    }
-    if (a.mask && wave == 0)
-        __builtin_amdgcn_global_load_lds(
-            reinterpret_cast<const void*>(a.mask + (size_t)b * a.max_seq + start + (lane < nkeys ? lane : 0)),
-            (__attribute__((address_space(3))) void*)mst, 4, 0, 0);
-    for (int i = tid; i < r * D / 8; i += 256)
-        reinterpret_cast<u32x4*>(qb)[i] =
-            *reinterpret_cast<const u32x4*>(a.q + ((size_t)b * a.nq + g * r) * D + i * 8);
-    __syncthreads();           // also: the stage loads have landed
-
-    const int n16 = lane & 15, q4 = lane >> 4;
-    const int gw = wave >> 1, part = wave & 1;
-    const float LOG2E = 1.4426950408889634f;
-    if (gw < ng) {
-        // S^T of tiles t = 0, 1: A row n16 of tile t is key 32 gw + 8 (n16 / 4)
-        // + 4 t + n16 % 4, so register j of lane (n16, q4) is key 8 q4 + 4 t + j
-        // of the group, head n16
-        f32x4 sacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-        const int row0 = 32 * gw + 8 * (n16 >> 2) + (n16 & 3), row1 = row0 + 4;
-        const unsigned char* K0 = Kst + (size_t)row0 * D * 2;
-        const unsigned char* K1 = Kst + (size_t)row1 * D * 2;
-        const uint16_t* qsrc = qb + (n16 < r ? n16 : 0) * D + 8 * q4;
+    // A row n16 of score tile t is key 8 (n16 / 4) + 4 t + n16 % 4 of the
+    // wave's 32, so register j of lane (n16, q4) is key 8 q4 + 4 t + j, head n16
+    u32x4 kr[2][NS], vr[NV];
+    auto load_stage = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < D / 32; s++) {
-            const u32x4 w = *reinterpret_cast<const u32x4*>(qsrc + 32 * s);
-            const bf16x8 qf = __builtin_bit_cast(bf16x8, n16 < r ? w : u32x4{0u, 0u, 0u, 0u});
-            const bf16x8 k0 = *reinterpret_cast<const bf16x8*>(K0 + (((4 * s + q4) ^ kswz(row0)) << 4));
-            const bf16x8 k1 = *reinterpret_cast<const bf16x8*>(K1 + (((4 * s + q4) ^ kswz(row1)) << 4));
-            sacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, qf, sacc[0], 0, 0, 0);
-            sacc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, qf, sacc[1], 0, 0, 0);
+        for (int t = 0; t < 2; t++) {
+            const int key = k0 + 8 * (n16 >> 2) + 4 * t + (n16 & 3);
+            const uint16_t* src = kc + (size_t)(key < end ? key : start) * D + 8 * q4;
+#pragma unroll
+            for (int s = 0; s < NS; s++) kr[t][s] = *reinterpret_cast<const u32x4*>(src + 32 * s);
         }
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const int key = k0 + i * KROWS + lane / NCK;
+            vr[i] = *reinterpret_cast<const u32x4*>(vc + (size_t)(key < end ? key : start) * D + (lane % NCK) * 8);
+        }
+    };
+    int k0 = start + 32 * wave;
+    u32x4 qw[NS];
+    const uint16_t* qsrc = a.q + ((size_t)b * a.nq + g * r + (n16 < r ? n16 : 0)) * D + 8 * q4;
+#pragma unroll
+    for (int s = 0; s < NS; s++) qw[s] = *reinterpret_cast<const u32x4*>(qsrc + 32 * s);
+    load_stage(k0);
+    bf16x8 qf[NS];
+#pragma unroll
+    for (int s = 0; s < NS; s++) qf[s] = __builtin_bit_cast(bf16x8, n16 < r ? qw[s] : u32x4{0u, 0u, 0u, 0u});
+
+    f32x4 o[D / 16];
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    for (; k0 < end; k0 += DEC_ST) {
+        float mk[8];
+        if (a.mask) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const int key = k0 + 8 * q4 + e;
+                mk[e] = a.mask[(size_t)b * a.max_seq + (key < end ? key : start)];
+            }
+        }
+        f32x4 sacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+            sacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[0][s]), qf[s], sacc[0], 0, 0, 0);
+            sacc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[1][s]), qf[s], sacc[1], 0, 0, 0);
+        }
+        // V to LDS (its readers below are this wave alone, so no barrier; a
+        // wave's LDS operations are served in order)
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const int row = i * KROWS + lane / NCK;
+            *reinterpret_cast<u32x4*>(Vst + (size_t)row * D * 2 + (((lane % NCK) ^ vswz(row)) << 4)) = vr[i];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        load_stage(k0 + DEC_ST);          // (past the end: the share's first row, never used)
         float sv[8];
         float mx = -INFINITY;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-            const int kk = 32 * gw + 8 * q4 + e;
             float v = sacc[e / 4][e % 4] * a.scale_log2;
-            if (a.mask) v += mst[kk] * LOG2E;
-            v = kk < nkeys ? v : -INFINITY;
+            if (a.mask) v += mk[e] * LOG2E;
+            v = k0 + 8 * q4 + e < end ? v : -INFINITY;
             sv[e] = v;
             mx = fmaxf(mx, v);
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m, mx);
+        const float mb = m_new == -INFINITY ? 0.f : m_new;     // (every key so far masked: all weights 0)
+        const float alpha = exp2_hw(m - mb);
         bf16x8 phi, plo;
         float ls = 0.f;
-        const float mb = mx == -INFINITY ? 0.f : mx;     // (every key masked: all weights 0)
 #pragma unroll
         for (int e = 0; e < 8; e++) {
             const float pv = exp2_hw(sv[e] - mb);
@@ -413,111 +443,124 @@ __global__ void __launch_bounds__(256) attn_decode_split_kernel(AttnDecodeArgs a
         }
         ls += __shfl_xor(ls, 16, 64);
         ls += __shfl_xor(ls, 32, 64);
-        // O^T += V^T P^T over this wave's half of the 16-dim blocks: lane
-        // (n16, q4) holds V of keys 8 q4 .. + 7, dim 16 db + n16
-        // (two transposing reads: lane n16 of its group points at key
-        // 8 q4 + n16 / 4 (+ 4), dims 16 db + 4 (n16 % 4) .. + 3, in their
-        // swizzled chunk)
-        const uint16_t* Vw = reinterpret_cast<const uint16_t*>(Vst + (size_t)(32 * gw + 8 * q4 + (n16 >> 2)) * D * 2);
+        l = l * alpha + ls;
+        m = m_new;
+        // O^T += V^T P^T per 16-dim block db: lane (n16, q4) holds V of keys
+        // 8 q4 .. + 7, dim 16 db + n16 (two transposing reads: lane n16 of its
+        // group points at key 8 q4 + n16 / 4 (+ 4), dims 16 db + 4 (n16 % 4) .. + 3,
+        // in their swizzled chunk)
+        const uint16_t* Vw = reinterpret_cast<const uint16_t*>(Vst + (size_t)(8 * q4 + (n16 >> 2)) * D * 2);
 #pragma unroll
-        for (int d0 = 0; d0 < D / 32; d0++) {
-            const int db = part * (D / 32) + d0;
+        for (int db = 0; db < D / 16; db++) {
             const int off = (((2 * db + ((n16 & 3) >> 1)) ^ (2 * q4)) << 3) | (4 * (n16 & 1));
             const i16x4 v0 = lds_read_tr16(Vw + off), v1 = lds_read_tr16(Vw + 4 * D + off);
             const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-            f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-            o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, phi, o, 0, 0, 0);
-            o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, plo, o, 0, 0, 0);
-            if (n16 < r) *reinterpret_cast<f32x4*>(ored + (gw * MAXR + n16) * D + 16 * db + 4 * q4) = o;
+#pragma unroll
+            for (int e = 0; e < 4; e++) o[db][e] *= alpha;
+            o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, phi, o[db], 0, 0, 0);
+            o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, plo, o[db], 0, 0, 0);
         }
-        if (n16 < r && q4 == 0 && part == 0) {
-            gst[(gw * MAXR + n16) * 2] = mx;
-            gst[(gw * MAXR + n16) * 2 + 1] = ls;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+
+    // ---- the waves' states meet in LDS: outputs over the V stages
+    __syncthreads();
+    float* const ored = reinterpret_cast<float*>(smem);          // [DEC_W][MAXR][D]
+    if (n16 < r) {
+#pragma unroll
+        for (int db = 0; db < D / 16; db++)
+            *reinterpret_cast<f32x4*>(ored + (wave * MAXR + n16) * D + 16 * db + 4 * q4) = o[db];
+        if (q4 == 0) {
+            gst[wave][n16][0] = m;
+            gst[wave][n16][1] = l;
         }
     }
     __syncthreads();
-    // the chunk partial of every head: the groups rescaled to their common max
-    for (int idx = tid; idx < r * D; idx += 256) {
-        const int i = idx / D, dim = idx - i * D;
-        const float m0 = gst[i * 2], m1 = ng > 1 ? gst[(MAXR + i) * 2] : -INFINITY;
-        const float M = fmaxf(m0, m1);
-        float v = 0.f, l = 0.f;
-        if (M != -INFINITY) {
-            const float s0 = m0 == -INFINITY ? 0.f : exp2f(m0 - M);
-            const float s1 = m1 == -INFINITY ? 0.f : exp2f(m1 - M);
-            v = s0 * ored[i * D + dim] + (ng > 1 ? s1 * ored[(MAXR + i) * D + dim] : 0.f);
-            l = s0 * gst[i * 2 + 1] + (ng > 1 ? s1 * gst[(MAXR + i) * 2 + 1] : 0.f);
-        }
-        float* pp = a.part + (((size_t)b * a.nq + g * r + i) * a.nchunks + chunk) * (D + 2);
-        pp[dim] = v;
-        if (dim == 0) { pp[D] = M; pp[D + 1] = l; }
-    }
-}
-
-// Merge of the chunk partials of one (row, head): thread group gq (of
-// DEC_CG groups of D threads, one thread per dim) merges the chunks
-// gq, gq + DEC_CG, ... in order, in batches of CB whose states are requested
-// together; the groups' states then meet in LDS and group 0 merges them in
-// group order.
-constexpr int DEC_CG = 4;
-
-template <int D>
-__global__ void __launch_bounds__(D * DEC_CG) attn_decode_combine_kernel(AttnDecodeArgs a) {
-    __shared__ float gm[DEC_CG], gl[DEC_CG], go[DEC_CG][D];
-    const int b = blockIdx.x / a.nq, head = blockIdx.x % a.nq;
-    const int dim = threadIdx.x % D, gq = threadIdx.x / D;
-    const int ctx = a.ctx_lens ? a.ctx_lens[b] : a.ctx_base + b;
-    const int nch = (ctx + 1 + a.chunk - 1) / a.chunk;
-    const float* pp = a.part + ((size_t)b * a.nq + head) * a.nchunks * (D + 2);
-    constexpr int CB = 8;
-    float M = -INFINITY, L = 0.f, O = 0.f;
-    for (int c0 = gq; c0 < nch; c0 += CB * DEC_CG) {
-        float mc[CB], lc[CB], oc[CB];
-#pragma unroll
-        for (int j = 0; j < CB; j++) {
-            const int ch0 = c0 + j * DEC_CG;
-            const int ch = ch0 < nch ? ch0 : gq;
-            mc[j] = pp[ch * (D + 2) + D];
-            lc[j] = pp[ch * (D + 2) + D + 1];
-            oc[j] = pp[ch * (D + 2) + dim];
-        }
-        float Mn = M;
-#pragma unroll
-        for (int j = 0; j < CB; j++)
-            if (c0 + j * DEC_CG < nch) Mn = fmaxf(Mn, mc[j]);
-        if (Mn == -INFINITY) continue;
-        const float sc = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
-        L *= sc;
-        O *= sc;
-#pragma unroll
-        for (int j = 0; j < CB; j++) {
-            if (c0 + j * DEC_CG >= nch || mc[j] == -INFINITY) continue;
-            const float w = exp2f(mc[j] - Mn);
-            L += w * lc[j];
-            O += w * oc[j];
-        }
-        M = Mn;
-    }
-    if (dim == 0) { gm[gq] = M; gl[gq] = L; }
-    go[gq][dim] = O;
-    __syncthreads();
-    if (gq != 0) return;
-    float Mt = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < DEC_CG; q++) Mt = fmaxf(Mt, gm[q]);
-    float Lt = 0.f, Ot = 0.f;
-    if (Mt != -INFINITY) {
-#pragma unroll
-        for (int q = 0; q < DEC_CG; q++) {
-            if (gm[q] == -INFINITY) continue;
-            const float w = exp2f(gm[q] - Mt);
-            Lt += w * gl[q];
-            Ot += w * go[q][dim];
-        }
-    }
-    const float v = (Lt > 0.f) ? Ot / Lt : 0.f;
+    // share state: [row, kv head][share][r heads][D] outputs, then [..][r][2] (max, sum)
+    const size_t tile = (size_t)blockIdx.x * a.nsplit;
+    unsigned long long* const po = reinterpret_cast<unsigned long long*>(a.part) + tile * r * (D / 2);
+    unsigned long long* const pst = reinterpret_cast<unsigned long long*>(a.part) +
+                                    (size_t)gridDim.x * a.nsplit * r * (D / 2) + tile * r;
+    auto pack = [](float x, float y) { return (unsigned long long)__float_as_uint(y) << 32 | __float_as_uint(x); };
+    f16* const out = a.out + ((size_t)b * a.nq + g * r) * D;
     bool bad = false;
-    a.out[((size_t)b * a.nq + head) * D + dim] = act_f16(v, bad);
+    auto put = [&](int idx, float x, float y, float lt) __attribute__((always_inline)) {     // output pair idx
+        const f16 h0 = act_f16(lt > 0.f ? x / lt : 0.f, bad), h1 = act_f16(lt > 0.f ? y / lt : 0.f, bad);
+        reinterpret_cast<uint32_t*>(out)[idx] =
+            (uint32_t)__builtin_bit_cast(uint16_t, h0) | (uint32_t)__builtin_bit_cast(uint16_t, h1) << 16;
+    };
+    for (int idx = tid; idx < r * (D / 2); idx += 64 * DEC_W) {
+        const int i = idx / (D / 2);
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < DEC_W; w++) M = fmaxf(M, gst[w][i][0]);
+        float x = 0.f, y = 0.f, lt = 0.f;
+#pragma unroll
+        for (int w = 0; w < DEC_W; w++) {
+            const float sc = gst[w][i][0] == -INFINITY ? 0.f : exp2f(gst[w][i][0] - M);
+            const float2 v = *reinterpret_cast<const float2*>(ored + w * MAXR * D + 2 * idx);
+            x += sc * v.x;
+            y += sc * v.y;
+            lt += sc * gst[w][i][1];
+        }
+        if (n == 1) {
+            put(idx, x, y, lt);
+        } else {
+            __hip_atomic_store(po + (size_t)part * r * (D / 2) + idx, pack(x, y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (idx % (D / 2) == 0)
+                __hip_atomic_store(pst + part * r + i, pack(M, lt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (n > 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's stores are complete
+        __syncthreads();
+        if (tid == 0)
+            last_flag = __hip_atomic_fetch_add(a.cnt + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
+                        (unsigned)n;
+        __syncthreads();
+        if (!last_flag) return;
+        // the statistics of all shares and the outputs of the first CB are
+        // requested together: one memory round trip
+        constexpr int CB = 16;
+        unsigned long long v[CB];
+        auto load_v = [&](int idx, int c0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < CB; c++)
+                v[c] = __hip_atomic_load(po + (size_t)(c0 + c < n ? c0 + c : n - 1) * r * (D / 2) + idx,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        const int idx0 = tid < r * (D / 2) ? tid : 0;
+        unsigned long long s0 = 0;
+        if (tid < n * r) s0 = __hip_atomic_load(pst + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        load_v(idx0, 0);
+        float2* const st = reinterpret_cast<float2*>(smem);     // [share][r] (max, sum)
+        if (tid < n * r) st[tid] = float2{__uint_as_float((unsigned)s0), __uint_as_float((unsigned)(s0 >> 32))};
+        for (int i = tid + 64 * DEC_W; i < n * r; i += 64 * DEC_W) {
+            const unsigned long long u = __hip_atomic_load(pst + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            st[i] = float2{__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32))};
+        }
+        __syncthreads();
+        for (int idx = tid; idx < r * (D / 2); idx += 64 * DEC_W) {
+            const int i = idx / (D / 2);
+            float M = -INFINITY;
+            for (int c = 0; c < n; c++) M = fmaxf(M, st[c * r + i].x);
+            float x = 0.f, y = 0.f, lt = 0.f;
+            for (int c0 = 0; c0 < n; c0 += CB) {
+                if (c0 > 0 || idx != tid) load_v(idx, c0);
+#pragma unroll
+                for (int c = 0; c < CB; c++) {
+                    if (c0 + c >= n) break;
+                    const float2 s = st[(c0 + c) * r + i];
+                    if (s.x == -INFINITY) continue;
+                    const float w = exp2f(s.x - M);
+                    lt += w * s.y;
+                    x += w * __uint_as_float((unsigned)v[c]);
+                    y += w * __uint_as_float((unsigned)(v[c] >> 32));
+                }
+            }
+            put(idx, x, y, lt);
+        }
+    }
     flag_range(a.err, bad);
 }
 
@@ -579,17 +622,38 @@ int launch_attn_prefill(const AttnPrefillArgs& a, const AttnPrefillPlan& p, hipS
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// Shares per (row, kv head): the count with the least estimated time.  A stage
+// costs a block about 1.3 us (a memory round trip and its arithmetic), a
+// second share the hand-off (store, count, read back: three round trips) and a
+// little for every state merged.
+int attn_decode_splits(int B, int nkv, int max_ctx, int num_cus) {
+    const int stages = (int)(((long long)max_ctx + DEC_ST) / DEC_ST);
+    int best = 1;
+    double best_cost = -1.0;
+    for (int n = 1; n <= stages && (n == 1 || (long long)B * nkv * n <= num_cus); n++) {
+        const long long rounds = ((long long)B * nkv * n + num_cus - 1) / num_cus;
+        const double cost = 1.3 * rounds * ((stages + n - 1) / n) + (n > 1 ? 3.0 + 0.08 * n : 0.0);
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best = n;
+        }
+    }
+    return best;
+}
+
 int launch_attn_decode(const AttnDecodeArgs& a, hipStream_t stream) {
-    if (a.chunk != DEC_CH || a.nq / a.nkv > MAXR) return -1;
-    dim3 g1(a.B * a.nkv, a.nchunks), g2(a.B * a.nq);
-    // K and V stages, the two groups' outputs and statistics, mask values, q
-    const size_t lds = (size_t)2 * DEC_CH * a.d * 2 + (2 * MAXR * a.d + 4 * MAXR + DEC_CH) * 4 + (size_t)MAXR * a.d * 2;
+    const int r = a.nq / a.nkv;
+    if (r > MAXR || a.nsplit < 1 || (a.nsplit > 1 && (!a.part || !a.cnt))) return -1;
+    const dim3 grid(a.B * a.nkv, a.nsplit);
+    // V stages of the waves; over them their outputs, then the shares' statistics
+    const size_t lds = std::max({(size_t)DEC_W * 32 * a.d * 2, (size_t)DEC_W * MAXR * a.d * 4, (size_t)a.nsplit * r * 8});
+    static LdsLimit lim128, lim64;
     if (a.d == 128) {
-        hipLaunchKernelGGL(attn_decode_split_kernel<128>, g1, dim3(256), lds, stream, a);
-        hipLaunchKernelGGL(attn_decode_combine_kernel<128>, g2, dim3(128 * DEC_CG), 0, stream, a);
+        if (ensure_lds_limit(lim128, (const void*)attn_decode_kernel<128>, lds)) return -1;
+        hipLaunchKernelGGL(attn_decode_kernel<128>, grid, dim3(64 * DEC_W), lds, stream, a);
     } else if (a.d == 64) {
-        hipLaunchKernelGGL(attn_decode_split_kernel<64>, g1, dim3(256), lds, stream, a);
-        hipLaunchKernelGGL(attn_decode_combine_kernel<64>, g2, dim3(64 * DEC_CG), 0, stream, a);
+        if (ensure_lds_limit(lim64, (const void*)attn_decode_kernel<64>, lds)) return -1;
+        hipLaunchKernelGGL(attn_decode_kernel<64>, grid, dim3(64 * DEC_W), lds, stream, a);
     } else {
         return -1;
     }

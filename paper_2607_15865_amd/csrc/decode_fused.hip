@@ -313,18 +313,18 @@ __global__ void __launch_bounds__(NTHR) decode_fused_kernel(DecodeFusedArgs a) {
 
     // one ring per product, sized for its usual run length; a product's ring
     // is filled as soon as the previous product's tiles are all consumed
-    TileRing<RING_QKV, false> R1;
-    TileRing<RING_O, false> R3;
-    TileRing<RING, false> R4, R5;
+    TileRing<RING_QKV> R1;
+    TileRing<RING_O> R3;
+    TileRing<RING> R4, R5;
     RunCursor q1, q3, q4, q5;
     auto prefetch = [&](int ph) {
         if (!owns(ph)) return;
         const Run run = wave_run(ph);
         if (run.ka >= run.kz) return;
-        if (ph == 1) ring_prefetch<RING_QKV, false, false>(a.qkv, run, R1, q1);
-        if (ph == 3) ring_prefetch<RING_O, false, false>(a.o, run, R3, q3);
-        if (ph == 4) ring_prefetch<RING, false, false>(a.gu, run, R4, q4);
-        if (ph == 5) ring_prefetch<RING, false, false>(a.down, run, R5, q5);
+        if (ph == 1) ring_prefetch<RING_QKV>(a.qkv, run, R1, q1);
+        if (ph == 3) ring_prefetch<RING_O>(a.o, run, R3, q3);
+        if (ph == 4) ring_prefetch<RING>(a.gu, run, R4, q4);
+        if (ph == 5) ring_prefetch<RING>(a.down, run, R5, q5);
     };
     // this wave's part of the block partial of slot `slot`
     auto to_red = [&](int slot, const float (&out)[4]) {
@@ -388,9 +388,9 @@ __global__ void __launch_bounds__(NTHR) decode_fused_kernel(DecodeFusedArgs a) {
         norm_prep_rows(hbuf, gam_lds ? gam : a.attn_norm, a.eps, B, H, xs, ldx, c64, red8, a.err);
         stamp_done(6);
         clear_red();
-        const GemvAct xa{xs, ldx, c64, nullptr, zero64};
+        const GemvAct xa{xs, ldx, c64, zero64};
         if (run1.ka < run1.kz)
-            gemv_run<RING_QKV, false, false, MAXB == 1>(a.qkv, run1, xa, B, R1, q1, [&](int, const float (&out)[4]) { to_red(0, out); });
+            gemv_run<RING_QKV, MAXB == 1>(a.qkv, run1, xa, B, R1, q1, [&](int, const float (&out)[4]) { to_red(0, out); });
         stamp_done(7);
         __syncthreads();
         for (int i = tid; i < B * 32; i += NTHR) {
@@ -746,12 +746,12 @@ __global__ void __launch_bounds__(NTHR) decode_fused_kernel(DecodeFusedArgs a) {
         stamp_done(11);
         clear_red();
         if (tid < 8) reinterpret_cast<u32x4*>(zero64)[tid] = u32x4{0u, 0u, 0u, 0u};   // (attention reused it)
-        gemv_prep(xs - klo, ldx, c64 - ka3 * GEMV_ROWS, nullptr, B, klo, 2 * kh, tid, NTHR);
+        gemv_prep(xs - klo, ldx, c64 - ka3 * GEMV_ROWS, B, klo, 2 * kh, tid, NTHR);
         __syncthreads();
         stamp_done(19);
-        const GemvAct xa{xs - klo, ldx, c64 - ka3 * GEMV_ROWS, nullptr, zero64};
+        const GemvAct xa{xs - klo, ldx, c64 - ka3 * GEMV_ROWS, zero64};
         if (run3.ka < run3.kz)
-            gemv_run<RING_O, false, false, MAXB == 1>(a.o, run3, xa, B, R3, q3, [&](int, const float (&out)[4]) { to_red(0, out); });
+            gemv_run<RING_O, MAXB == 1>(a.o, run3, xa, B, R3, q3, [&](int, const float (&out)[4]) { to_red(0, out); });
         stamp_done(20);
         __syncthreads();
         stamp_done(21);
@@ -775,9 +775,9 @@ __global__ void __launch_bounds__(NTHR) decode_fused_kernel(DecodeFusedArgs a) {
         norm_prep_rows(hbuf, gam_lds ? gam + H : a.mlp_norm, a.eps, B, H, xs, ldx, c64, red8, a.err);
         stamp_done(22);
         clear_red();
-        const GemvAct xa{xs, ldx, c64, nullptr, zero64};
+        const GemvAct xa{xs, ldx, c64, zero64};
         if (run4.ka < run4.kz)
-            gemv_run<RING, false, false, MAXB == 1>(a.gu, run4, xa, B, R4, q4,
+            gemv_run<RING, MAXB == 1>(a.gu, run4, xa, B, R4, q4,
                                          [&](int t, const float (&out)[4]) { to_red(t - ta4, out); });
         stamp_done(13);
         __syncthreads();
@@ -810,11 +810,11 @@ __global__ void __launch_bounds__(NTHR) decode_fused_kernel(DecodeFusedArgs a) {
         stamp_done(14);
         clear_red();
         if (tid < 8) reinterpret_cast<u32x4*>(zero64)[tid] = u32x4{0u, 0u, 0u, 0u};   // (attention reused it)
-        gemv_prep(xs - klo, ldx, c64 - ka5 * GEMV_ROWS, nullptr, B, klo, 2 * kh, tid, NTHR);
+        gemv_prep(xs - klo, ldx, c64 - ka5 * GEMV_ROWS, B, klo, 2 * kh, tid, NTHR);
         __syncthreads();
-        const GemvAct xa{xs - klo, ldx, c64 - ka5 * GEMV_ROWS, nullptr, zero64};
+        const GemvAct xa{xs - klo, ldx, c64 - ka5 * GEMV_ROWS, zero64};
         if (run5.ka < run5.kz)
-            gemv_run<RING, false, false, MAXB == 1>(a.down, run5, xa, B, R5, q5, [&](int, const float (&out)[4]) { to_red(0, out); });
+            gemv_run<RING, MAXB == 1>(a.down, run5, xa, B, R5, q5, [&](int, const float (&out)[4]) { to_red(0, out); });
         stamp_done(15);
         __syncthreads();
         if (s5 > 0) {

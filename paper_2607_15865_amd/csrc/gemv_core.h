@@ -1,5 +1,7 @@
-// Decode GEMV core: one wave's walk over a run of weight tiles, for B <= 8
-// activation rows (the decode batch).
+// Decode GEMV core, for B <= 8 activation rows (the decode batch): the
+// fragment forms and corrections shared by the decode GEMV (gemv_w4.hip) and
+// the persistent decode, and the persistent decode's walk of one wave over a
+// run of weight tiles.
 //
 // A run is the set of tiles (t, kb) with column tile t in [t0, t1) and k-tile
 // kb in [ka, kz), walked column by column.  The wave streams the tiles
@@ -12,12 +14,17 @@
 // (code - zero): each code pair becomes the fp16 pair it makes when OR-ed
 // into 0x6400 (dequant8_raw, five bit operations per word), which is
 // 1024 + q for the codes in bits 0..3 of a byte and 1024 + 16 q for the codes
-// in bits 4..7.  The activations are prepared to match (gemv_prep): the
-// elements at k % 8 in {2, 3, 6, 7} (the bits 4..7 codes) are divided by 16,
-// and per row and 32-k segment the sums E (other elements) and O (divided
-// elements) are kept.  The product over a segment is then
+// in bits 4..7.  The activations are prepared to match: the elements at
+// k % 8 in {2, 3, 6, 7} (the bits 4..7 codes) are divided by 16, and per row
+// and 64-k tile (32-k segment with groups of 32) the sums E (other elements)
+// and O (divided elements) are kept.  The product over it is then
 //     sum x'(raw) = sum x (q - z) + 1024 (E + O) + z (E + 16 O),
-// so one subtraction per output recovers the exact-weight sum.
+// so one subtraction per output recovers the exact-weight sum.  The 8- and
+// 16-bit formats take the same activations x'.  INT8: the fragment pairs are
+// 0x64 | code = 1024 + q at k % 8 in {0, 1, 4, 5} and 0x74 | code =
+// 16 (1024 + q) at the divided elements, so the product over a tile is
+// sum x (q - z) + (1024 + z) (E + 16 O).  F16: the divided elements' weights
+// are held times 16, so the product is the exact-weight sum (scale 1).
 //
 // The product runs on the 16x16x32 fp16 MFMA with the 32-column tile as is:
 // lane l of the B operand is the lane's word s (column 32 t + l % 32,
@@ -30,9 +37,8 @@
 // 32 t + l % 32: the lane's own column, so the lane's own group scale
 // applies.  Four 16-cycle MFMAs per tile instead of four 32-cycle ones.
 //
-// Group parameters: the raw fp16 scale bits (or scale | zero << 16 when the
-// linear has zero points, ZP) of the group of k 0..31 of a tile, and with
-// groups of 32 (G32) also of k 32..63, travel with the tile in the ring.
+// The group parameters of a tile, the raw fp16 scale bits (or scale | zero
+// << 16 when the linear has zero points), travel with the tile in the ring.
 #pragma once
 #include "common.h"
 
@@ -70,10 +76,6 @@ constexpr int GEMV_ROWS = 8;     // row stride of the correction tables
 //   xs[b * ldx + k]                       x' (fp16), rows b < B;
 //   c64[(k / 64) * GEMV_ROWS + b]         1024 (E + O) + 8 (E + 16 O) over the
 //                                         64-k tile (the correction for z = 8);
-//   uv32[(k / 32) * GEMV_ROWS + b]        (E + O, E + 16 O) over the 32-k
-//                                         segment (any zero point); may be
-//                                         null when only z = 8 with groups of
-//                                         64 or more is used;
 //   zero                                  64 zero fp16 (the A operand of the
 //                                         lanes whose column half does not
 //                                         match).
@@ -81,7 +83,6 @@ struct GemvAct {
     const f16* xs;
     int ldx;
     const float* c64;
-    const float2* uv32;
     const f16* zero;
 };
 
@@ -93,11 +94,11 @@ __device__ __forceinline__ float gemv_c64(float e, float o) {
 
 // Prepare rows b < B, absolute k in [k0, k0 + klen) (klen a multiple of 64)
 // in place: x (bf16 values held as fp16) -> x', and write the correction
-// tables (pointers as in GemvAct, non-const).  One 8-element chunk per thread
+// table (pointers as in GemvAct, non-const).  One 8-element chunk per thread
 // and pass; the 8 chunks of a 64-k tile sit in 8 adjacent lanes, which meet
 // with DPP row operations.  Called by all nthr threads of the block (nthr a
 // multiple of 64); the caller synchronises before and after.
-__device__ __forceinline__ void gemv_prep(f16* xs, int ldx, float* c64, float2* uv32, int B, int k0, int klen,
+__device__ __forceinline__ void gemv_prep(f16* xs, int ldx, float* c64, int B, int k0, int klen,
                                           int tid, int nthr) {
     const int nc = klen >> 3, total = B * nc;
     const f16x2 sixteenth = f16x2{(f16)0.0625f, (f16)0.0625f};
@@ -120,25 +121,22 @@ __device__ __forceinline__ void gemv_prep(f16* xs, int ldx, float* c64, float2* 
             o = ((float)x1[0] + (float)x1[1]) + ((float)x3[0] + (float)x3[1]);
             *p = u32x4{w0, __builtin_bit_cast(uint32_t, x1), w2, __builtin_bit_cast(uint32_t, x3)};
         }
-        // sums over the 4 chunks of a 32-k segment, then the 8 of a 64-k tile
+        // sums over the 8 chunks of a 64-k tile
         e += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(e), 0xB1, 0xF, 0xF, false));
         o += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o), 0xB1, 0xF, 0xF, false));
         e += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(e), 0x4E, 0xF, 0xF, false));
         o += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o), 0x4E, 0xF, 0xF, false));
-        if (uv32 && ok && (c & 3) == 0) uv32[(k >> 5) * GEMV_ROWS + b] = float2{e + o, e + 16.0f * o};
         e += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(e), 0x141, 0xF, 0xF, false));
         o += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o), 0x141, 0xF, 0xF, false));
         if (ok && (c & 7) == 0) c64[(k >> 6) * GEMV_ROWS + b] = gemv_c64(e, o);
     }
 }
 
-// D tiles of a lane: quad j of tile slot u in w[u][j] (1, 2 or 4 quads
-// for the 4-, 8- and 16-bit formats).
-template <int D, bool G32, int WF = WF_INT4>
+// D tiles of a lane (4-bit weights) and their scales.
+template <int D>
 struct TileRing {
-    u32x4 w[D][1 << WF];
+    u32x4 w[D];
     uint32_t sa[D];
-    uint32_t sb[G32 ? D : 1];
 };
 
 struct Run {
@@ -147,16 +145,16 @@ struct Run {
 };
 
 // Wave-uniform position in a run: the tile's byte offset in the tile array,
-// the element offset of its group parameters (group row + column), and kb.
+// the element offset of its group scales (group row + column), and kb.
 struct RunCursor {
-    uint32_t woff;     // ((t * KBf + kb) * tile bytes (1024 << wf))
+    uint32_t woff;     // (t * KBf + kb) * 1024
     uint32_t grow;     // (kb * 64 >> lgG) * N_dev
     uint32_t gcol;     // t * 32
     int kb;
 
     __device__ __forceinline__ void start(const DevLinear& W, const Run& run) {
         const int KBf = W.K_pad >> 6;
-        woff = (uint32_t)(run.t0 * KBf + run.ka) << (10 + W.wf);
+        woff = (uint32_t)(run.t0 * KBf + run.ka) << 10;
         grow = (uint32_t)((run.ka * 64) >> W.lgG) * (uint32_t)W.N_dev;
         gcol = (uint32_t)run.t0 * 32u;
         kb = run.ka;
@@ -165,12 +163,11 @@ struct RunCursor {
     __device__ __forceinline__ void next(const DevLinear& W, const Run& run) {
         const int KBf = W.K_pad >> 6;
         kb++;
-        woff += 1024u << W.wf;
-        if (W.lgG < 6) grow += (uint32_t)W.N_dev << (6 - W.lgG);   // groups of 32: two per tile
-        else if (((kb * 64) & ((1 << W.lgG) - 1)) == 0) grow += (uint32_t)W.N_dev;
+        woff += 1024u;
+        if (((kb * 64) & ((1 << W.lgG) - 1)) == 0) grow += (uint32_t)W.N_dev;
         if (kb == run.kz) {
             kb = run.ka;
-            woff += (uint32_t)(KBf - (run.kz - run.ka)) << (10 + W.wf);
+            woff += (uint32_t)(KBf - (run.kz - run.ka)) << 10;
             grow = (uint32_t)((run.ka * 64) >> W.lgG) * (uint32_t)W.N_dev;
             gcol += 32u;
         }
@@ -178,21 +175,11 @@ struct RunCursor {
 };
 
 // Load the tile at cursor q into slot u.
-template <int D, bool ZP, bool G32, int WF = WF_INT4>
-__device__ __forceinline__ void ring_load(const DevLinear& W, TileRing<D, G32, WF>& R, int u, const RunCursor& q) {
+template <int D>
+__device__ __forceinline__ void ring_load(const DevLinear& W, TileRing<D>& R, int u, const RunCursor& q) {
     const int lane = threadIdx.x & 63;
-    const uint32_t lo = (uint32_t)lane * 16u;
-#pragma unroll
-    for (int j = 0; j < (1 << WF); j++)
-        R.w[u][j] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(W.qw) + (q.woff + 1024u * j + lo));
-    const uint32_t gi = q.grow + q.gcol + (uint32_t)(lane & 31);
-    if (ZP) R.sa[u] = W.sz[gi];
-    else R.sa[u] = W.scales[gi];
-    if (G32) {   // the k 32..63 half starts a new group
-        const uint32_t gj = gi + (uint32_t)W.N_dev;
-        if (ZP) R.sb[G32 ? u : 0] = W.sz[gj];
-        else R.sb[G32 ? u : 0] = W.scales[gj];
-    }
+    R.w[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(W.qw) + (q.woff + (uint32_t)lane * 16u));
+    R.sa[u] = W.scales[q.grow + q.gcol + (uint32_t)(lane & 31)];
 }
 
 // Fill the ring with the first D tiles of the run; the cursor q is left at
@@ -201,16 +188,15 @@ __device__ __forceinline__ void ring_load(const DevLinear& W, TileRing<D, G32, W
 // first tile again (a cache hit): ring slots are written unconditionally, so
 // no slot value has to be merged across branches (that would force a wait
 // for the load).
-template <int D, bool ZP, bool G32, int WF = WF_INT4>
-__device__ __forceinline__ void ring_prefetch(const DevLinear& W, const Run& run, TileRing<D, G32, WF>& R,
-                                              RunCursor& q) {
+template <int D>
+__device__ __forceinline__ void ring_prefetch(const DevLinear& W, const Run& run, TileRing<D>& R, RunCursor& q) {
     const int n = run.size();
     RunCursor first;
     first.start(W, run);
     q = first;
 #pragma unroll
     for (int u = 0; u < D; u++) {
-        ring_load<D, ZP, G32, WF>(W, R, u, u < n ? q : first);
+        ring_load(W, R, u, u < n ? q : first);
         q.next(W, run);
     }
 }
@@ -239,17 +225,9 @@ __device__ __forceinline__ float gzero(uint32_t v) {
 // stores its results would make any later wait that covers it (the wait
 // before the ring's registers are reused) also wait for those stores to
 // complete.
-//
-// The 8- and 16-bit formats (WF) take the same activations x'.  INT8: the B
-// fragment pairs are 0x64 | code = 1024 + q at k % 8 in {0, 1, 4, 5} and
-// 0x74 | code = 16 (1024 + q) at the divided elements, so the product over
-// a 64-k tile is sum x (1024 + q) = sum x (q - z) + (1024 + z) S with S the
-// tile's sum of x (E + 16 O over its two 32-k segments): one correction per
-// output with the column's zero point.  F16: the divided elements' weights
-// are held times 16, so the product is the exact-weight sum (scale 1).
-template <int D, bool ZP, bool G32, bool DRAIN = false, typename Emit, int WF = WF_INT4>
-__device__ __forceinline__ void gemv_run(const DevLinear& W, const Run& run, const GemvAct& xa, int B,
-                                         TileRing<D, G32, WF>& R, RunCursor& q, Emit&& emit) {
+template <int D, bool DRAIN = false, typename Emit>
+__device__ __forceinline__ void gemv_run(const DevLinear& W, const Run& run, const GemvAct& xa, int B, TileRing<D>& R,
+                                         RunCursor& q, Emit&& emit) {
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const DqConst dq = dq_const();
     // A operand of this lane: MFMA row m = lane % 16 (batch row bm, column
@@ -274,59 +252,13 @@ __device__ __forceinline__ void gemv_run(const DevLinear& W, const Run& run, con
                 const f16x8 a2 = *reinterpret_cast<const f16x8*>(xk + 32);
                 const f16x8 a3 = *reinterpret_cast<const f16x8*>(xk + 48);
                 const float sa = gscale(R.sa[u]);
-                if constexpr (WF == WF_INT8) {
-                    f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, dequant8_u8_raw(R.w[u][0][0], R.w[u][0][1]), zero, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, dequant8_u8_raw(R.w[u][0][2], R.w[u][0][3]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a2, dequant8_u8_raw(R.w[u][1][0], R.w[u][1][1]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a3, dequant8_u8_raw(R.w[u][1][2], R.w[u][1][3]), acc, 0, 0, 0);
-                    const float zc = 1024.0f + gzero<true>(R.sa[u]);
-                    const float2* uv = xa.uv32 + (2 * pkb) * GEMV_ROWS + 4 * h;
-                    const float2* uw = uv + GEMV_ROWS;
+                f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, dequant8_raw(R.w[u][0], dq), zero, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, dequant8_raw(R.w[u][1], dq), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a2, dequant8_raw(R.w[u][2], dq), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a3, dequant8_raw(R.w[u][3], dq), acc, 0, 0, 0);
+                const f32x4_t cc = *reinterpret_cast<const f32x4_t*>(xa.c64 + pkb * GEMV_ROWS + 4 * h);
 #pragma unroll
-                    for (int r = 0; r < 4; r++) out[r] = __builtin_fmaf(sa, acc[r] - zc * (uv[r].y + uw[r].y), out[r]);
-                } else if constexpr (WF == WF_F16) {
-                    f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, __builtin_bit_cast(f16x8, R.w[u][0]), zero, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, __builtin_bit_cast(f16x8, R.w[u][1]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a2, __builtin_bit_cast(f16x8, R.w[u][2]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a3, __builtin_bit_cast(f16x8, R.w[u][3]), acc, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; r++) out[r] += acc[r];
-                } else {
-                f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, dequant8_raw(R.w[u][0][0], dq), zero, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, dequant8_raw(R.w[u][0][1], dq), acc, 0, 0, 0);
-                if (G32) {
-                    // k 0..31 and k 32..63 are two groups
-                    const float za = gzero<ZP>(R.sa[u]);
-                    const float sb = gscale(R.sb[G32 ? u : 0]), zb = gzero<ZP>(R.sb[G32 ? u : 0]);
-                    const float2* uv = xa.uv32 + (2 * pkb) * GEMV_ROWS + 4 * h;
-#pragma unroll
-                    for (int r = 0; r < 4; r++)
-                        out[r] = __builtin_fmaf(sa, acc[r] - __builtin_fmaf(za, uv[r].y, 1024.0f * uv[r].x), out[r]);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a2, dequant8_raw(R.w[u][0][2], dq), zero, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a3, dequant8_raw(R.w[u][0][3], dq), acc, 0, 0, 0);
-                    const float2* uw = uv + GEMV_ROWS;
-#pragma unroll
-                    for (int r = 0; r < 4; r++)
-                        out[r] = __builtin_fmaf(sb, acc[r] - __builtin_fmaf(zb, uw[r].y, 1024.0f * uw[r].x), out[r]);
-                } else {
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a2, dequant8_raw(R.w[u][0][2], dq), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a3, dequant8_raw(R.w[u][0][3], dq), acc, 0, 0, 0);
-                    if (ZP) {
-                        const float za = gzero<ZP>(R.sa[u]);
-                        const float2* uv = xa.uv32 + (2 * pkb) * GEMV_ROWS + 4 * h;
-                        const float2* uw = uv + GEMV_ROWS;
-#pragma unroll
-                        for (int r = 0; r < 4; r++) {
-                            const float cr = __builtin_fmaf(za, uv[r].y + uw[r].y, 1024.0f * (uv[r].x + uw[r].x));
-                            out[r] = __builtin_fmaf(sa, acc[r] - cr, out[r]);
-                        }
-                    } else {
-                        const f32x4_t cc = *reinterpret_cast<const f32x4_t*>(xa.c64 + pkb * GEMV_ROWS + 4 * h);
-#pragma unroll
-                        for (int r = 0; r < 4; r++) out[r] = __builtin_fmaf(sa, acc[r] - cc[r], out[r]);
-                    }
-                }
-                }
+                for (int r = 0; r < 4; r++) out[r] = __builtin_fmaf(sa, acc[r] - cc[r], out[r]);
                 if (pkb == run.kz - 1) {
                     emit(pt, out);
 #pragma unroll
@@ -339,9 +271,9 @@ __device__ __forceinline__ void gemv_run(const DevLinear& W, const Run& run, con
             }
             // refill the slot with tile base + u + D (or the first tile)
             if constexpr (DRAIN) {
-                if (base + u + D < n) ring_load<D, ZP, G32, WF>(W, R, u, q);
+                if (base + u + D < n) ring_load(W, R, u, q);
             } else {
-                ring_load<D, ZP, G32, WF>(W, R, u, base + u + D < n ? q : first);
+                ring_load(W, R, u, base + u + D < n ? q : first);
             }
             q.next(W, run);
         }

@@ -80,11 +80,19 @@ struct GemvArgs {
     int ldx;
     int B;
     int ksplit;              // blocks along K
+    int ct;                  // residual: column tiles per block (1 or 2)
+    int num_cus;             // of the device: the block shape
+    int off_red;             // set by the launcher
     EpiArgs ep;
-    const float* copy_src;   // optional side copy (fp32), count copy_n
-    float* copy_dst;
-    int copy_n;
+    float* clear;            // fp32 words that the launch sets to zero (the output that a later
+    int nclear;              // launch adds into), nclear of them
+    unsigned* zero;          // words that the launch sets to zero (arrival counters of a later
+    int nzero;               // launch), nzero of them
 };
+// the fused RMSNorm of B rows of K fits the GEMV block's registers
+bool gemv_norm_fits(int B, int K);
+// sets ct and ksplit of a residual GEMV (from W, B, num_cus)
+void gemv_resid_plan(GemvArgs& a, bool ordered);
 int launch_gemv_w4(int epi, bool norm, const GemvArgs& a, hipStream_t stream);
 
 // zero, nzero: words that the launch also sets to zero (arrival counters of
@@ -125,12 +133,14 @@ struct AttnDecodeArgs {
     int ctx_base;
     const float* mask;       // [B][max_seq] or null
     int max_seq;
-    float* part;             // [B][nq][nchunks][d + 2]
+    float* part;             // share states, B * nq * nsplit * (d + 2) floats (nsplit > 1)
+    unsigned* cnt;           // [B][nkv] arrival counters, zeroed by an earlier launch (nsplit > 1)
     f16* out;                // [B][nq*d]
-    int B, nq, nkv, d, chunk, nchunks;
+    int B, nq, nkv, d, nsplit;   // nsplit: shares of a (row, kv head)'s keys
     float scale_log2;
     int* err;                // the layer's error flag (W4_FLAG_F16_RANGE)
 };
+int attn_decode_splits(int B, int nkv, int max_ctx, int num_cus);
 int launch_attn_decode(const AttnDecodeArgs& a, hipStream_t stream);
 
 int launch_kv_append(uint16_t* k_cache, uint16_t* v_cache, const uint16_t* k_new, const uint16_t* v_new,
