@@ -6,19 +6,23 @@
 // those queries see; its waves are the query heads of the kv head's group
 // (one head per wave), so every K/V tile staged in LDS serves all of them.
 // Chunks split long key ranges across blocks (a causal prefill's late query
-// tiles, a prefill_kv over a long history), so the grid has enough blocks;
-// work items are ordered longest first.
+// tiles, a prefill_kv over a long history) where the grid would leave CUs idle
+// (attn_prefill_plan); work items are ordered longest first.
 //
-// Keys are staged 64 at a time (two 32-key tiles), K and V both straight
-// from memory to LDS (direct-to-LDS loads), double buffered: one memory round
-// trip per 64 keys, one barrier.  K rows are 16-byte-chunk XOR-swizzled by
-// row (conflict-free fragment reads); V stays in its natural [key][dim]
-// layout and the V^T fragments of O^T = V^T P^T come from it by transposing
-// LDS reads (lds_read_tr16).  Scores are formed transposed, S^T = K Q^T, with the 32 key rows
-// of a tile fed in a permuted order (bits 2 and 3 of the row index swapped)
-// so that register e of the score tile holds key 16*(e/8) + 8*(lane/32) +
-// e%8 of query lane%32: exactly the operand layout of P^T.  Every lane
-// therefore owns one query: the online softmax (running max and sum) lives
+// Keys are staged 64 at a time (two 32-key tiles), double buffered, one barrier
+// per stage.  K and V of the next stage are on their way into registers while
+// the current one is computed, and go to LDS at its end.  (As direct-to-LDS
+// loads they were waited for in the middle of the stage: the compiler takes the
+// transposing reads of V as possible readers of a load in flight and puts
+// vmcnt(0) before them.  Head size 64, and blocks of fewer than 4 waves, whose
+// share of a stage their registers would not hold, still load that way.)  K rows are 16-byte-chunk XOR-swizzled by row
+// (conflict-free fragment reads); V stays in its natural [key][dim] layout and
+// the V^T fragments of O^T = V^T P^T come from it by transposing LDS reads
+// (lds_read_tr16).  Scores are formed transposed, S^T = K Q^T, with the 32 key
+// rows of a tile fed in a permuted order (bits 2 and 3 of the row index
+// swapped) so that register e of the score tile holds key 16*(e/8) +
+// 8*(lane/32) + e%8 of query lane%32: exactly the operand layout of P^T.  Every
+// lane therefore owns one query: the online softmax (running max and sum) lives
 // in registers; the max moves only when a score passes it by more than 8
 // (log2 units), so the weights stay below 2^8.  P is fed to the MFMA as a
 // bf16 pair hi + lo (P - hi), which keeps P V at near-fp32 accuracy.  The
@@ -75,10 +79,19 @@ __device__ __forceinline__ size_t part_index(const AttnPrefillArgs& a, int row, 
     return ((size_t)(row * a.items + item) * PF_MAXHB + wave) * NREG * 64 + lane;
 }
 
-template <int D>
+// ML: 1 KB stage loads per wave (K and V together) at most; 0: direct-to-LDS
+// loads (blocks of few waves; d = 64, whose smaller registers let two blocks of
+// 7 waves share a CU: 700 tokens of Qwen-0.5B 21 us either way, 1500 over 500
+// 36 against 40).  Bound by the latency of a stage's chain (scores, softmax, P V) with
+// two waves per SIMD: 1.7 us a stage with one block per CU, 2.4 with two
+// (d = 128).
+template <int D, int ML>
 __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefillArgs a) {
     constexpr int NCH = D / 8;               // 16-byte chunks per K / V row
     constexpr int STB = PF_KST * D * 2;      // bytes of one K or V stage
+    constexpr int NT = 2;                    // 32-key tiles per stage
+    constexpr int KROWS = 1024 / (2 * D);    // rows per load
+    constexpr int NLOAD = PF_KST / KROWS;    // loads per K or V stage
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* const Ks = smem;              // [2][64 keys][D], chunks swizzled
     unsigned char* const Vs = smem + 2 * STB;    // [2][64 keys][D]
@@ -101,23 +114,39 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
     const uint16_t* kc = a.k_cache + (size_t)g * a.cache_stride_h;
     const uint16_t* vc = a.v_cache + (size_t)g * a.cache_stride_h;
 
-    // ---- stage of 64 keys: 2 x 64 loads of 1 KB (K, V); load i fills rows
-    // KROWS i .. + KROWS - 1; lane l writes chunk l % NCH of its row (for K
-    // holding logical chunk (l % NCH) ^ (row % NCH))
-    constexpr int KROWS = 1024 / (2 * D);
-    constexpr int NLOAD = PF_KST / KROWS;
+    // ---- stage of 64 keys: 2 NLOAD loads of 1 KB (K, then V), wave w takes
+    // loads w, w + HB, ..; load i fills rows KROWS i .. + KROWS - 1; lane l holds
+    // chunk l % NCH of its row (for K logical chunk (l % NCH) ^ (row % NCH))
+    u32x4 sr[ML ? ML : 1];
+    auto stage_src = [&](int i, int st) __attribute__((always_inline)) {
+        const bool isv = i >= NLOAD;
+        const int row = (isv ? i - NLOAD : i) * KROWS + lane / NCH;
+        int slot = k0 + st * PF_KST + row;
+        slot = slot < k1 ? slot : k1 - 1;
+        const int pc = lane % NCH, lc = isv ? pc : pc ^ (row % NCH);
+        return (isv ? vc : kc) + (size_t)slot * D + lc * 8;
+    };
+    auto stage_dst = [&](int i, int buf) __attribute__((always_inline)) {
+        return i >= NLOAD ? Vs + buf * STB + (i - NLOAD) * 1024 : Ks + buf * STB + i * 1024;
+    };
     auto load_stage = [&](int st, int buf) __attribute__((always_inline)) {
-        for (int i = wave; i < NLOAD; i += HB) {
-            const int row = i * KROWS + lane / NCH;
-            int slot = k0 + st * PF_KST + row;
-            slot = slot < k1 ? slot : k1 - 1;
-            const int pc = lane % NCH, lc = pc ^ (row % NCH);
-            __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(kc + (size_t)slot * D + lc * 8),
-                                             (__attribute__((address_space(3))) void*)(Ks + buf * STB + i * 1024),
-                                             16, 0, 0);
-            __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(vc + (size_t)slot * D + pc * 8),
-                                             (__attribute__((address_space(3))) void*)(Vs + buf * STB + i * 1024),
-                                             16, 0, 0);
+        if constexpr (ML == 0) {
+            for (int i = wave; i < 2 * NLOAD; i += HB)
+                __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(stage_src(i, st)),
+                                                 (__attribute__((address_space(3))) void*)stage_dst(i, buf), 16, 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < ML; j++) {
+                const int i = wave + j * HB;
+                if (i < 2 * NLOAD) sr[j] = *reinterpret_cast<const u32x4*>(stage_src(i, st));
+            }
+        }
+    };
+    auto store_stage = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < ML; j++) {
+            const int i = wave + j * HB;
+            if (i < 2 * NLOAD) *reinterpret_cast<u32x4*>(stage_dst(i, buf) + lane * 16) = sr[j];
         }
     };
 
@@ -136,6 +165,7 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
     float m = -INFINITY, l = 0.f;
     const int qslot = a.L + qrow;
     const int krow = key_perm(c);
+    store_stage(0);
     __syncthreads();
     for (int st = 0; st < nst; st++) {
         const int buf = st & 1;
@@ -143,33 +173,36 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
         if (active) {
             const unsigned char* K = Ks + buf * STB;
             const __bf16* V = reinterpret_cast<const __bf16*>(Vs + buf * STB);
-            // S^T of the two 32-key tiles, two independent MFMA chains
-            f32x16 sa = f32x16{}, sb = f32x16{};
+            // S^T of the wave's 32-key tiles, independent MFMA chains
+            f32x16 sc[NT];
+#pragma unroll
+            for (int t = 0; t < NT; t++) sc[t] = f32x16{};
 #pragma unroll
             for (int s = 0; s < D / 16; s++) {
                 const int lc = (2 * s + h) ^ (krow % NCH);
-                const bf16x8 ka = *reinterpret_cast<const bf16x8*>(K + krow * (2 * D) + lc * 16);
-                const bf16x8 kb = *reinterpret_cast<const bf16x8*>(K + (32 + krow) * (2 * D) + lc * 16);
-                sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[s], sa, 0, 0, 0);
-                sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb, qf[s], sb, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < NT; t++) {
+                    const bf16x8 kf = *reinterpret_cast<const bf16x8*>(K + (32 * t + krow) * (2 * D) + lc * 16);
+                    sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sc[t], 0, 0, 0);
+                }
             }
             const int kbase = k0 + st * PF_KST;
-            const bool diag = kbase + PF_KST - 1 > a.L + q0;
-            float p[32];
+            const bool diag = kbase + 32 * NT - 1 > a.L + q0;
+            float p[16 * NT];
 #pragma unroll
-            for (int e = 0; e < 32; e++) p[e] = (e < 16 ? sa[e] : sb[e - 16]) * a.scale_log2;
+            for (int e = 0; e < 16 * NT; e++) p[e] = sc[e / 16][e % 16];
             if (diag) {            // (only the stages that straddle the diagonal)
 #pragma unroll
-                for (int e = 0; e < 32; e++) {
+                for (int e = 0; e < 16 * NT; e++) {
                     const int kslot = kbase + 32 * (e / 16) + 16 * ((e % 16) / 8) + 8 * h + (e % 8);
                     if (kslot > qslot) p[e] = -INFINITY;
                 }
             }
             float mt = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < 32; e++) mt = fmaxf(mt, p[e]);
+            for (int e = 0; e < 16 * NT; e++) mt = fmaxf(mt, p[e]);
             mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-            const float m_new = fmaxf(m, mt);
+            const float m_new = fmaxf(m, mt * a.scale_log2);       // (log2 units)
             // The running max m moves (and o, l are rescaled) only when some
             // lane's scores pass it by more than 8 (log2 units); until then the
             // weights are taken against the older m and stay below 2^8, which
@@ -185,16 +218,16 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
                 m = m_new;
             }
             const float mb = m == -INFINITY ? 0.f : m;
-            float ls = 0.f;
+            float ls[4] = {0.f, 0.f, 0.f, 0.f};          // (four chains)
 #pragma unroll
-            for (int e = 0; e < 32; e++) {
-                p[e] = exp2_hw(p[e] - mb);
-                ls += p[e];
+            for (int e = 0; e < 16 * NT; e++) {
+                p[e] = exp2_hw(__builtin_fmaf(p[e], a.scale_log2, -mb));
+                ls[e % 4] += p[e];
             }
-            l += ls;
-            // O^T += V^T P^T over the 4 key groups of 16 (tile, step)
+            l += (ls[0] + ls[1]) + (ls[2] + ls[3]);
+            // O^T += V^T P^T over the key groups of 16 (tile, step)
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++) {
+            for (int ks = 0; ks < 2 * NT; ks++) {
                 bf16x8 phi, plo;
 #pragma unroll
                 for (int j = 0; j < 8; j += 2) {          // pairs: one packed conversion each
@@ -217,12 +250,14 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
                 }
             }
         }
+        if (st + 1 < nst) store_stage(buf ^ 1);
         __syncthreads();
     }
+
     if (!active) return;
 
     if (nch == 1) {
-        // output: dim of register e of o[i] is i * 32 + 8 (e / 4) + 4 h + e % 4
+        // output: dim of register e of block i is i * 32 + 8 (e / 4) + 4 h + e % 4
         if (qrow >= a.T) return;
         const float lt = l + __shfl_xor(l, 32, 64);
         const float inv = (lt > 0.f) ? 1.f / lt : 0.f;
@@ -231,11 +266,16 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
 #pragma unroll
         for (int i = 0; i < D / 32; i++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) out[i * 32 + 8 * (e / 4) + 4 * h + (e % 4)] = act_f16(o[i][e] * inv, bad);
+            for (int e = 0; e < 16; e += 4) {
+                f16 v[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) v[j] = act_f16(o[i][e + j] * inv, bad);
+                *reinterpret_cast<uint2*>(out + i * 32 + 2 * e + 4 * h) = *reinterpret_cast<const uint2*>(v);
+            }
         flag_range(a.err, bad);
         return;
     }
-    // partial state of this chunk: [row][item][wave][m, l, O registers][64 lanes]
+    // partial state of this chunk: [row][item][head][m, l, O registers][64 lanes]
     float* pp = a.part + part_index<D>(a, blockIdx.y, blockIdx.x, wave, lane);
     pp[0] = m;
     pp[64] = l;
@@ -248,7 +288,9 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_kernel(AttnPrefill
 // Merge of the chunk states of the query tiles with more than one chunk:
 // block (query tile, block row, 32-dim slice): thread (wave, lane) merges the
 // lane's 16 output registers of the slice over the tile's chunks, in order.
-template <int D>
+// CB chunks are requested together: 4, or 8 for tiles of more than 8 chunks
+// (64 tokens over 4000, 16 chunks; short tiles would only read more).
+template <int D, int CB>
 __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_merge_kernel(AttnPrefillArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int HB = blockDim.x / 64;
@@ -264,7 +306,6 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_merge_kernel(AttnP
     if (nch == 1 || hidx >= r) return;
     // chunks in groups of CB: the states of a group are requested together,
     // then merged into the running maximum M, sum L and output acc
-    constexpr int CB = 4;
     float M = -INFINITY, L = 0.f, acc[16] = {};
     for (int ch0 = 0; ch0 < nch; ch0 += CB) {
         float mc[CB], lc[CB], v[CB][16];
@@ -303,7 +344,12 @@ __global__ void __launch_bounds__(64 * PF_MAXHB) attn_prefill_merge_kernel(AttnP
     f16* out = a.out + ((size_t)qrow * a.nq + g * r + hidx) * D;
     bool bad = false;
 #pragma unroll
-    for (int e = 0; e < 16; e++) out[i * 32 + 8 * (e / 4) + 4 * h + (e % 4)] = act_f16(acc[e] * inv, bad);
+    for (int e = 0; e < 16; e += 4) {
+        f16 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = act_f16(acc[e + j] * inv, bad);
+        *reinterpret_cast<uint2*>(out + i * 32 + 2 * e + 4 * h) = *reinterpret_cast<const uint2*>(v);
+    }
     flag_range(a.err, bad);
 }
 
@@ -573,15 +619,45 @@ AttnPrefillPlan attn_prefill_plan(int T, int L, int nq, int nkv, int d, int num_
     p.ngrp = (r + hb - 1) / hb;
     p.threads = 64 * hb;
     const int nqt = (T + 31) / 32;
-    // key stages of all query tiles of one block row, then chunks of at
-    // least 2 stages (128 keys) sized so that the grid holds about two
-    // blocks per CU
-    long long stages = 0;
-    for (int qt = 0; qt < nqt; qt++) stages += (L + std::min(T, 32 * (qt + 1)) + PF_KST - 1) / PF_KST;
     const long long rows = (long long)nkv * p.ngrp;
-    long long cs = (stages * rows + 2LL * num_cus - 1) / (2LL * num_cus);
-    cs = std::max(2LL, cs);
-    p.chunk_keys = (int)(PF_KST * cs);
+    const int nreg = 2 + 16 * (d / 32);
+    // Key chunk (in stages, at least 2): the one with the least estimated time,
+    // in us.  A stage takes a block t, or t2 where blocks share CUs (up to two of
+    // 4 waves do) or take turns; a block's start and end count as one stage more;
+    // chunks cost the merge launch, its passes over a tile's chunks, and the
+    // write and read of their states at about 5.5 TB/s.  Fitted to the chunks of 2 to 32 stages at 16 (T, L) of the
+    // Llama-8B, Qwen-7B and Qwen-0.5B layers; against grids of about two blocks
+    // per CU, attention and merge: Llama-8B, 1000 tokens 44.1 -> 39.0 us, 64
+    // over 4000 33.5 -> 26.1, Qwen-7B, 2011 tokens 114.7 -> 89.2, 100 over 3000
+    // 41.1 -> 30.6.
+    const double t = d == 64 ? 1.5 : hb > 4 ? 2.2 : 1.7, t2 = (d == 64 ? 1.2 : 1.4) * t;
+    const long long slots = (long long)num_cus * (p.threads <= 256 || d == 64 ? 2 : 1);
+    const int smax = (L + T + PF_KST - 1) / PF_KST;
+    double best = -1.0;
+    int cs = 2;
+    for (int c = 2;; c += c < 8 ? 1 : c / 4) {
+        long long blocks = 0, parts = 0, total = 0;
+        for (int qt = 0; qt < nqt; qt++) {
+            const int st = (L + std::min(T, 32 * (qt + 1)) + PF_KST - 1) / PF_KST, n = (st + c - 1) / c;
+            blocks += n;
+            parts += n > 1 ? n : 0;
+            total += st;
+        }
+        blocks *= rows;
+        parts *= rows;
+        total *= rows;
+        const double longest = std::min(c, smax) + 1.0;
+        double us = blocks <= num_cus ? t * longest
+                    : blocks <= slots ? t2 * longest
+                                      : t2 * std::max(longest, (double)(total + blocks) / (double)slots + longest);
+        if (parts) us += 3.5 + 0.2 * ((smax + c - 1) / c) + (double)parts * hb * nreg * 512.0 / 5.5e6;
+        if (best < 0 || us < best) {
+            best = us;
+            cs = c;
+        }
+        if (c >= smax) break;
+    }
+    p.chunk_keys = PF_KST * cs;
     p.items = 0;
     bool multi = false;
     for (int qt = 0; qt < nqt; qt++) {
@@ -590,13 +666,22 @@ AttnPrefillPlan attn_prefill_plan(int T, int L, int nq, int nkv, int d, int num_
         multi |= n > 1;
     }
     p.merge = multi;
-    const int nreg = 2 + 16 * (d / 32);
     const size_t per_item = (size_t)rows * PF_MAXHB * nreg * 64 * sizeof(float);
     p.part_bytes = multi ? (size_t)p.items * per_item : 0;
     // chunks are at least 128 keys: a bound that grows with L, for workspace sizing
     p.part_bound = (size_t)nqt * ((L + T + 127) / 128) * per_item;
     p.lds_bytes = (size_t)4 * PF_KST * d * 2;
     return p;
+}
+
+template <int D, int ML>
+static int launch_prefill(const AttnPrefillArgs& a, const AttnPrefillPlan& p, dim3 grid, hipStream_t stream) {
+    // (every wave's share of a stage's loads fits its registers)
+    if (ML && p.threads / 64 * ML < 2 * PF_KST * D * 2 / 1024) return -1;
+    static LdsLimit lim;
+    if (ensure_lds_limit(lim, (const void*)attn_prefill_kernel<D, ML>, p.lds_bytes)) return -1;
+    hipLaunchKernelGGL((attn_prefill_kernel<D, ML>), grid, dim3(p.threads), p.lds_bytes, stream, a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_attn_prefill(const AttnPrefillArgs& a, const AttnPrefillPlan& p, hipStream_t stream) {
@@ -607,17 +692,16 @@ int launch_attn_prefill(const AttnPrefillArgs& a, const AttnPrefillPlan& p, hipS
     b.items = p.items;
     const dim3 grid(p.items, a.nkv * p.ngrp);
     const dim3 mgrid((a.T + 31) / 32, a.nkv * p.ngrp, a.d / 32);
-    static LdsLimit lim128, lim64;
-    if (a.d == 128) {
-        if (ensure_lds_limit(lim128, (const void*)attn_prefill_kernel<128>, p.lds_bytes)) return -1;
-        hipLaunchKernelGGL(attn_prefill_kernel<128>, grid, dim3(p.threads), p.lds_bytes, stream, b);
-        if (p.merge) hipLaunchKernelGGL(attn_prefill_merge_kernel<128>, mgrid, dim3(p.threads), 0, stream, b);
-    } else if (a.d == 64) {
-        if (ensure_lds_limit(lim64, (const void*)attn_prefill_kernel<64>, p.lds_bytes)) return -1;
-        hipLaunchKernelGGL(attn_prefill_kernel<64>, grid, dim3(p.threads), p.lds_bytes, stream, b);
-        if (p.merge) hipLaunchKernelGGL(attn_prefill_merge_kernel<64>, mgrid, dim3(p.threads), 0, stream, b);
-    } else {
-        return -1;
+    if (a.d != 128 && a.d != 64) return -1;
+    int rc;
+    if (a.d == 64) rc = launch_prefill<64, 0>(b, p, grid, stream);
+    else rc = p.threads >= 256 ? launch_prefill<128, 8>(b, p, grid, stream) : launch_prefill<128, 0>(b, p, grid, stream);
+    if (rc) return rc;
+    if (p.merge) {
+        const bool many = a.L + a.T > 8 * p.chunk_keys;
+        auto fn = a.d == 128 ? (many ? attn_prefill_merge_kernel<128, 8> : attn_prefill_merge_kernel<128, 4>)
+                             : (many ? attn_prefill_merge_kernel<64, 8> : attn_prefill_merge_kernel<64, 4>);
+        hipLaunchKernelGGL(fn, mgrid, dim3(p.threads), 0, stream, b);
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
