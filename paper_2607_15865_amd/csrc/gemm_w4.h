@@ -97,8 +97,9 @@ __host__ __device__ inline void split_range(int sp, int S, int KB, int& lo, int&
 // iteration); ZP: the linear has zero points; WF: weight format
 // (WeightFormat).  The 8- and 16-bit formats differ only in the tile bytes
 // (2 or 4 quads of 16 bytes per lane) and the fragment unpack (dequant8_u8,
-// f16_frag); their scales (one per column, in groups of 128) ride the same
-// ratio scheme (every ratio 1).
+// f16_frag); with one scale and zero point per column they need no ratios
+// (leaving out the multiplications by 1: INT8 Llama-8B, 800 rows, 496 -> 448 us
+// a layer, bf16 at 64 rows 144.5 -> 141.8).
 template <int EPI, int TM, int GT, bool ZP, int WF, int WN, int KG>
 __global__ void __launch_bounds__(64 * WN * KG) __attribute__((amdgpu_waves_per_eu(2)))
 gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, GemmShape gs) {
@@ -106,8 +107,8 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
     constexpr int XL = BM / (4 * WN);                   // X loads (1 KB) per wave and iteration
     constexpr int NH = GT == 0 ? 2 : 1;                 // group parameters per tile
     constexpr int RS = 8;                               // weight tile slots: two iterations
-    constexpr bool XREG = TM < 4;
-    static_assert(XREG || (WN == 4 && KG == 1), "row tiles of 128: four waves side by side");
+    constexpr bool XREG = TM < 4 && !(TM == 2 && WF == WF_F16);
+    static_assert(XREG || (WN == 4 && KG == 1), "X straight to LDS: four waves side by side");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned last_flag;
 
@@ -167,8 +168,9 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
     // Pipeline depth P: the loads of iteration it + P are requested in
     // iteration it.  Row tiles of 32 and 64 (short iterations) stage X in
     // registers, so the barrier of an iteration waits for LDS writes only and
-    // the deeper loads stay in flight; row tiles of 128 load X straight into
-    // LDS one iteration ahead (their registers hold the accumulators).
+    // the deeper loads stay in flight; row tiles of 128, and the 16-bit format's
+    // of 64, load X straight into LDS one iteration ahead (their registers hold
+    // the accumulators and weights).
     // (the 8- and 16-bit formats hold 2 or 4 times the weight registers per
     // tile: the shallowest pipeline)
     constexpr int P = WF != WF_INT4 ? 2 : TM == 1 ? (WN == 2 ? 3 : 4) : (TM == 2 && GT != 0 && WN == 4) ? 3 : 2;
@@ -221,6 +223,9 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
     // the q/k/v GEMM, whose exact sums decide the bf16 rounding of the
     // cached keys and values.
     constexpr bool FS = WF == WF_INT4 && TM == 4 && EPI != EPI_QKV;
+    // RT: ratios in use.  The 8- and 16-bit formats have one scale per column
+    // (every ratio 1) and one zero point, read once.
+    constexpr bool RT = WF == WF_INT4 && !FS;
     u32x4 rw[4 * NG][NQ];
     float rr[4 * NG][NH];
     f16 rs[4 * NG][NH];
@@ -235,8 +240,8 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
         for (int hh = 0; hh < NH; hh++) {
             const uint32_t gi = (uint32_t)((kk * 64 + 32 * hh) >> W.lgG) * (uint32_t)W.N_dev + (uint32_t)col;
             if constexpr (FS) rs[q][hh] = __builtin_bit_cast(f16, W.scales[gi]);
-            else rr[q][hh] = *reinterpret_cast<const float*>(Rb + gi * 4u);
-            if (ZP) rz[q][hh] = (uint32_t)W.zeros[gi];
+            else if constexpr (RT) rr[q][hh] = *reinterpret_cast<const float*>(Rb + gi * 4u);
+            if constexpr (RT && ZP) rz[q][hh] = (uint32_t)W.zeros[gi];
         }
     };
     // DMA variant: the scale ratio of the first tile of the iteration that
@@ -246,7 +251,7 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
     // iteration it + 2 from the start of iteration it on).
     float rn[2][2];
     auto load_rn = [&](int slot, int kb) __attribute__((always_inline)) {
-        if constexpr (FS) return;
+        if constexpr (!RT) return;
         const int kk = kb < kb_hi ? kb : kb_lo;
         const uint32_t g0 = (uint32_t)((kk * 64) >> W.lgG) * (uint32_t)W.N_dev;
         rn[slot][0] = *reinterpret_cast<const float*>(Rb + (g0 + (uint32_t)col0) * 4u);
@@ -263,6 +268,10 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
 #pragma unroll
     for (int i = 0; i < TM; i++) { acc[i][0] = f32x16{}; acc[i][1] = f32x16{}; }
     ZeroOff zo0 = zero_off(8.0f), zo1 = zo0;
+    if constexpr (WF == WF_INT8) {
+        zo0 = zero_off((float)W.zeros[col0]);
+        zo1 = zero_off((float)W.zeros[col1]);
+    }
     // A fragment of row tile i, step s, tile half: logical chunk 8 half + 2 s + h
     // of row 32 i + c, stored at chunk ^ (row & 15) (row & 15 == c & 15)
     const uint32_t arow = (uint32_t)c * 256u;
@@ -273,7 +282,7 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
         f16x8 a[2][TM], b[2][2];
         auto prep = [&](int t, int p) __attribute__((always_inline)) {
             const int half = t >> 2, s = t & 3, q = qb + 2 * half, hh = NH == 2 ? (s >> 1) : 0;
-            if (ZP && (s == 0 || (NH == 2 && s == 2))) {
+            if (ZP && WF == WF_INT4 && (s == 0 || (NH == 2 && s == 2))) {
                 zo0 = zero_off((float)rz[q][hh]);
                 zo1 = zero_off((float)rz[q + 1][hh]);
             }
@@ -313,7 +322,7 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
                 acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p][i], b[p][0], acc[i][0], 0, 0, 0);
                 acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p][i], b[p][1], acc[i][1], 0, 0, 0);
             }
-            if (!FS && next_group(t)) {
+            if (RT && next_group(t)) {
                 const int tn = (t + 1) & 7;                       // the next step
                 const int half = tn >> 2, hh = NH == 2 ? ((tn & 3) >> 1) : 0;
                 const int q = (t == 7 ? qn : qb) + 2 * half;
@@ -619,8 +628,8 @@ int launch_v(const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const
 template <int EPI, int TM, int GT, bool ZP, int WF>
 int launch_shape(const GemmPlan& p, const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmShape& gs,
                  hipStream_t stream) {
-    if constexpr (TM == 4) {
-        return launch_v<EPI, 4, GT, ZP, WF, 4, 1>(X, ldx, W, ep, gs, stream);
+    if constexpr (TM == 4 || (TM == 2 && WF == WF_F16)) {
+        return launch_v<EPI, TM, GT, ZP, WF, 4, 1>(X, ldx, W, ep, gs, stream);
     } else {
         if (p.WN == 4 && p.KG == 1) return launch_v<EPI, TM, GT, ZP, WF, 4, 1>(X, ldx, W, ep, gs, stream);
         if (p.WN == 4 && p.KG == 2) return launch_v<EPI, TM, GT, ZP, WF, 4, 2>(X, ldx, W, ep, gs, stream);
@@ -630,14 +639,14 @@ int launch_shape(const GemmPlan& p, const f16* X, int ldx, const DevLinear& W, c
     }
 }
 
-// row tiles of 128 only for groups of 64 or more without zero points, the
-// 16-bit format row tiles of 32; the other variants use at most 64
+// row tiles of 128 only for 4-bit weights in groups of 64 or more without zero
+// points (with them, and for the 8-bit format, they were built and measured: at
+// 200 to 800 rows slower than row tiles of 64 in all but one product)
 template <int EPI, int GT, bool ZP, int WF>
 int launch_tm(const GemmPlan& p, const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmShape& gs,
               hipStream_t stream) {
     if (p.TM == 1) return launch_shape<EPI, 1, GT, ZP, WF>(p, X, ldx, W, ep, gs, stream);
-    if constexpr (WF != WF_F16)
-        if (p.TM == 2) return launch_shape<EPI, 2, GT, ZP, WF>(p, X, ldx, W, ep, gs, stream);
+    if (p.TM == 2) return launch_shape<EPI, 2, GT, ZP, WF>(p, X, ldx, W, ep, gs, stream);
     if constexpr (WF == WF_INT4 && !ZP && GT != 0)
         if (p.TM == 4) return launch_shape<EPI, 4, GT, ZP, WF>(p, X, ldx, W, ep, gs, stream);
     return -1;

@@ -17,13 +17,18 @@
 // best against earlier: q/k/v 20.0 / 25.5 us, o_proj 18.5 / 19.7, gate/up
 // 40.8 / 48.1, down 29.7 / 36.7 (with events around each).
 //
+// The 16-bit format's row tiles of 64 load X straight to LDS (4-wave blocks of
+// 256 columns only); they take over where row tiles of 32 need a second round
+// of blocks or read the weights from L2 many times.  Llama-8B gate/up, row tiles
+// of 32 / 64: 64 rows 61 / 60 us, 100 85 / 72, 200 122 / 96, 400 185 / 149, 800
+// 306 / 236; q/k/v at 200 rows 40 / 42.
+//
 // Row tiles of 128 (which round the scaled weight to fp16 outside q/k/v) are
 // considered only from 0.75 tiles per CU on, 0.375 for k ranges of 12288 or more.
 GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
     const int its = W.K_pad / 128;
-    // the kernel variants that exist (the 16-bit format's weight registers
-    // leave room for row tiles of 32 only)
-    const int tm_max = W.wf == WF_F16 ? 1 : (W.zeros || W.lgG == 5 || W.wf != WF_INT4) ? 2 : 4;
+    // the kernel variants that exist
+    const int tm_max = W.zeros || W.lgG == 5 || W.wf != WF_INT4 ? 2 : 4;
     const double wf_cost = W.wf == WF_F16 ? 1.6 : W.wf == WF_INT8 ? 1.1 : W.zeros ? 1.05 : 1.0;
     const double x_cost = W.wf == WF_INT8 ? 0.14 : 0.057;
     GemmPlan best;
@@ -32,6 +37,7 @@ GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
         for (int shape = 0; shape < 3; shape++) {
             const int WN = shape == 2 ? 2 : 4, KG = shape == 0 ? 1 : shape == 1 ? 2 : 4;
             const int nrb = (M + 32 * TM - 1) / (32 * TM), ncb = (W.N_dev + 64 * WN - 1) / (64 * WN);
+            if (W.wf == WF_F16 && TM == 2 && KG > 1) continue;
             if (TM == 4) {
                 const int need = W.K_pad >= 12288 ? num_cus * 3 / 2 : num_cus * 3;
                 if (KG > 1 || nrb * ncb * 4 < need) continue;
@@ -41,7 +47,7 @@ GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
                 const long long blocks = (long long)nrb * ncb * S;
                 if (S > 1 && (its < 2 * S * KG || blocks > num_cus * 11 / 5)) break;
                 const double it = (its + S * KG - 1) / (S * KG) + 2;
-                const double us = (TM == 1 ? 0.61 : TM == 2 ? 0.88 : 1.33) * wf_cost;
+                const double us = (TM == 1 ? 0.61 : TM == 2 ? (W.wf == WF_F16 ? 0.78 : 0.88) : 1.33) * wf_cost;
                 const double usx = us + (WN == 2 ? x_cost * TM : 0.0);
                 const long long slots = (long long)num_cus * (KG == 1 ? 2 : 1), rest = blocks % slots;
                 double cost = (double)(blocks / slots) * it * usx;

@@ -23,7 +23,7 @@ SHAPES = {
 }
 FORMATS = {"int4": {}, "zeros": dict(with_zeros=True), "int8": dict(fmt="int8"), "bf16": dict(fmt="bf16")}
 CASES = ([("h256", "int4", T) for T in (9, 32, 33, 65, 127)] +
-         [("h896", f, T) for f, Ts in (("int4", (31, 64, 129, 300)), ("zeros", (33, 200)), ("int8", (65,)), ("bf16", (64, 97))) for T in Ts] +
+         [("h896", f, T) for f, Ts in (("int4", (31, 64, 129, 300)), ("zeros", (33, 200)), ("int8", (65,)), ("bf16", (64, 97, 300))) for T in Ts] +
          [("h1152", f, T) for f, Ts in (("int4", (9, 96, 257)), ("zeros", (64,)), ("int8", (10, 130)), ("bf16", (33,))) for T in Ts])
 
 
