@@ -425,14 +425,17 @@ int layer_debug_dequant(layer_t layer, int32_t which, float* out, void* stream);
 /* Decode implementation (tuning / testing): 0 automatic (default), 1 a
  * sequence of kernels, 2 one persistent launch with one block per CU (B <=
  * 4, INT4 weights without zero points in groups of 64 or more, and the
- * on-chip working set must fit; chosen automatically for B <= 2).  Both compute the same result up to
- * rounding order; the persistent path is deterministic, the kernel sequence
- * adds k-split partials with atomics.  With 2, a decode call the persistent
+ * on-chip working set must fit).  Automatic: such a layer's calls of one or
+ * two rows take whichever is faster at their size, all others the sequence.
+ * Both compute the same result up to rounding order.  The persistent path is
+ * deterministic, and so is the sequence where the automatic choice takes it in
+ * the persistent launch's place; otherwise the sequence adds k-split partials
+ * with atomics in any order.  With 2, a decode call the persistent
  * path cannot serve fails with W4_EUNSUPPORTED.  The decode kernels also
  * serve layer_prefill / layer_prefill_kv calls of a few tokens, the tokens
  * as rows of one sequence sharing its cache (row t also attends to the new
- * keys of rows before it): with path 0 up to 2 tokens as the persistent
- * launch and up to 8 as the kernel sequence, with path 2 up to 4 as the
+ * keys of rows before it): with path 0 up to 8 tokens (up to 2 as the
+ * persistent launch where that is faster), with path 2 up to 4 as the
  * persistent launch; path 1 keeps every prefill call on the prefill
  * kernels.  Errors: W4_EINVAL. */
 int layer_set_decode_path(layer_t layer, int32_t path);
@@ -478,7 +481,7 @@ int layer_debug_decode_stamps(layer_t layer, uint64_t* out, int32_t n);
  * layer_profile_kernel selects, for one stage, the kernel to time (stage 0 and
  * 1, prefill and prefill_kv: 0 rmsnorm, 1 qkv GEMM, 2 attention, 3 o_proj
  * GEMM, 4 rmsnorm, 5 gate/up GEMM, 6 down GEMM; stage 2, decode: 0 qkv GEMV,
- * 1 attention (split + combine), 3 o_proj GEMV, 4 gate/up GEMV, 5 down GEMV,
+ * 1 attention, 3 o_proj GEMV, 4 gate/up GEMV, 5 down GEMV,
  * 6 the whole persistent decode launch);
  * kernel < 0 switches timing of that stage off.  While selected, each stage
  * call records a HIP event pair around that launch on the call's stream (at

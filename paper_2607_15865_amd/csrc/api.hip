@@ -784,8 +784,12 @@ int run_decode_seq(layer_s* L, const float* x, const int32_t* pos, const int32_t
 // 300 52.3 / 46.8, 2000 58.6 / 49.7, 8000 83.3 / 56.6; Qwen-7B, 1 row, 300
 // 52.9 / 50.0, 8000 55.2 / 57.2; 2 rows, 2000 59.9 / 54.9; Qwen-0.5B, 1 row, 60
 // 31.6 / 29.5, 8000 33.3 / 38.2; 2 rows, 2000 36.7 / 34.8.  Layers narrower than
-// those (2 us apart) stay with the one launch.
+// those (2 us apart) stay with the one launch, and so do calls whose
+// diagnostics (stamps, poll budget, timing of the launch) ask for it.
 bool prefer_seq(const layer_s* L, int B, int max_ctx) {
+    if (L->decode_trace || L->spin_max != kSpinDefault || L->prof.kernel[0] == 7 || L->prof.kernel[1] == 7 ||
+        L->prof.kernel[2] == 6)
+        return false;
     return L->decode_path == 0 && L->cfg.hidden >= 512 && (B == 2 || max_ctx < 512);
 }
 
