@@ -36,7 +36,6 @@ namespace {
 constexpr int MAXB = 8;
 constexpr int NX = 4;            // 8-element activation chunks a thread holds
 constexpr int kRawBuffer = 0x00020000;       // buffer descriptor word 3: raw 32-bit data, stride 0
-constexpr uint32_t kPastEnd = 0xFFFF0000u;   // an offset past every buffer (linears stay below it)
 
 // WF: weight format (WeightFormat); the 8-bit format always has zero points (ZP)
 template <int EPI, bool NORM, bool ZP, bool G32, int WF, int NW, int CT>
@@ -111,8 +110,9 @@ __global__ void __launch_bounds__(NW * 64) gemv_w4_kernel(GemvArgs a) {
     // the run's first tile instead: INT8 Qwen-7B, 5 rows, 78.0 against 73.3 us a
     // layer, INT4 within 1%.)
     const uint32_t ngp = (uint32_t)W.KG * (uint32_t)W.N_dev;
+    const GemvRun wr = gemv_run_bytes(t0, CT, W.K_pad, WF);
     const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint32_t*>(W.qw), 0, (int)((uint32_t)(W.N_dev / 32 * KB) << (10 + WF)), kRawBuffer);
+        const_cast<uint32_t*>(W.qw) + wr.first / 4, 0, (int)wr.bytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
         ZP ? (void*)const_cast<uint32_t*>(W.sz) : (void*)const_cast<uint16_t*>(W.scales), 0, (int)(ngp * (ZP ? 4u : 2u)),
         kRawBuffer);
@@ -126,8 +126,8 @@ __global__ void __launch_bounds__(NW * 64) gemv_w4_kernel(GemvArgs a) {
         const uint32_t grow = (((uint32_t)kb * 64u) >> W.lgG) * (uint32_t)W.N_dev;
 #pragma unroll
         for (int t = 0; t < CT; t++) {
-            const uint32_t wo = kb < kz ? (uint32_t)((t0 + t) * KB + kb) << (10 + WF) : kPastEnd;
-            const uint32_t go = kb < kz ? (grow + (uint32_t)(t0 + t) * 32u) * GS : kPastEnd;
+            const uint32_t wo = kb < kz ? (uint32_t)(t * KB + kb) << (10 + WF) : kGemvPastEnd;
+            const uint32_t go = kb < kz ? (grow + (uint32_t)(t0 + t) * 32u) * GS : kGemvPastEnd;
 #pragma unroll
             for (int j = 0; j < NQ; j++) w[u][t][j] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wo + lw + 1024u * j, 0, 0);
             if (WF != WF_F16) sa[u][t] = load_param(go + lg);
@@ -441,6 +441,13 @@ void gemv_resid_plan(GemvArgs& a, bool ordered) {
 }
 
 bool gemv_norm_fits(int B, int K) { return B * ((K / 64 + 7) / 8) <= NX * 8; }
+
+// (for the host tests)
+extern "C" void w4_gemv_run_bytes(int tile, int ct, int K_pad, int wf, uint64_t* first, uint32_t* bytes) {
+    const GemvRun r = gemv_run_bytes(tile, ct, K_pad, wf);
+    *first = r.first;
+    *bytes = r.bytes;
+}
 
 int launch_gemv_w4(int epi, bool norm, const GemvArgs& a, hipStream_t stream) {
     if (a.B < 1 || a.B > MAXB) return -1;

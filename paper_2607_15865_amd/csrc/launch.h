@@ -89,6 +89,19 @@ struct GemvArgs {
     unsigned* zero;          // words that the launch sets to zero (arrival counters of a later
     int nzero;               // launch), nzero of them
 };
+// Weights that a GEMV block reads: those of ct column tiles from `tile` on, one
+// contiguous run of `bytes` from byte `first` of the matrix.  A block's buffer
+// covers just its run, so that its 32-bit offsets do not depend on the size of
+// the matrix (16-bit gate/up of hidden 16384, FFN 65536: exactly 4 GiB).
+struct GemvRun {
+    uint64_t first;
+    uint32_t bytes;
+};
+constexpr uint32_t kGemvPastEnd = 0xFFFF0000u;   // an offset past every block's run
+__host__ __device__ inline GemvRun gemv_run_bytes(int tile, int ct, int K_pad, int wf) {
+    const uint32_t strip = (uint32_t)(K_pad / 64) << (10 + wf);     // one column tile
+    return GemvRun{(uint64_t)(uint32_t)tile * strip, (uint32_t)ct * strip};
+}
 // the fused RMSNorm of B rows of K fits the GEMV block's registers
 bool gemv_norm_fits(int B, int K);
 // sets ct and ksplit of a residual GEMV (from W, B, num_cus)
