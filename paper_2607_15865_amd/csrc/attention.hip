@@ -374,8 +374,10 @@ constexpr int DEC_ST = 32 * DEC_W;   // keys per stage of a block (32 per wave)
 // are the columns (padded to 16); the key rows are fed in the order that
 // leaves the probabilities in the operand layout of P^T; P is a bf16 pair
 // hi + lo.  Every wave keeps a running max, sum and output; the waves meet in
-// LDS at the end.  Rows past the share's keys read its first row (a written
-// cache slot, so V stays finite) and get probability 0.
+// LDS at the end.  Rows past the share's keys read its last row (in the last
+// share the new token's, so V stays finite) and get probability 0.  Hidden slots
+// (mask -inf) may hold anything, a NaN of memory that was never written among
+// it: their scores are set, not added to, and their V rows become zeros.
 //
 // With more than one share the blocks store their states (device-coherent, as
 // the prefill GEMM's split sums) and count their arrival; the last one merges
@@ -410,18 +412,23 @@ __global__ void __launch_bounds__(64 * DEC_W) attn_decode_kernel(AttnDecodeArgs 
     // A row n16 of score tile t is key 8 (n16 / 4) + 4 t + n16 % 4 of the
     // wave's 32, so register j of lane (n16, q4) is key 8 q4 + 4 t + j, head n16
     u32x4 kr[2][NS], vr[NV];
+    float mk[8];                                                // mask of keys 8 q4 .. + 7
     auto load_stage = [&](int k0) __attribute__((always_inline)) {
+        if (a.mask) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) mk[e] = a.mask[(size_t)b * a.max_seq + min(k0 + 8 * q4 + e, end - 1)];
+        }
 #pragma unroll
         for (int t = 0; t < 2; t++) {
             const int key = k0 + 8 * (n16 >> 2) + 4 * t + (n16 & 3);
-            const uint16_t* src = kc + (size_t)(key < end ? key : start) * D + 8 * q4;
+            const uint16_t* src = kc + (size_t)min(key, end - 1) * D + 8 * q4;
 #pragma unroll
             for (int s = 0; s < NS; s++) kr[t][s] = *reinterpret_cast<const u32x4*>(src + 32 * s);
         }
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             const int key = k0 + i * KROWS + lane / NCK;
-            vr[i] = *reinterpret_cast<const u32x4*>(vc + (size_t)(key < end ? key : start) * D + (lane % NCK) * 8);
+            vr[i] = *reinterpret_cast<const u32x4*>(vc + (size_t)min(key, end - 1) * D + (lane % NCK) * 8);
         }
     };
     int k0 = start + 32 * wave;
@@ -439,19 +446,27 @@ __global__ void __launch_bounds__(64 * DEC_W) attn_decode_kernel(AttnDecodeArgs 
     for (int i = 0; i < D / 16; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
     for (; k0 < end; k0 += DEC_ST) {
-        float mk[8];
-        if (a.mask) {
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const int key = k0 + 8 * q4 + e;
-                mk[e] = a.mask[(size_t)b * a.max_seq + (key < end ? key : start)];
-            }
-        }
         f32x4 sacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int s = 0; s < NS; s++) {
             sacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[0][s]), qf[s], sacc[0], 0, 0, 0);
             sacc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[1][s]), qf[s], sacc[1], 0, 0, 0);
+        }
+        float ml[8];                                            // (log2 units)
+        uint32_t hidden = 0;
+        if (a.mask) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                ml[e] = mk[e] * LOG2E;
+                hidden |= (uint32_t)(ml[e] == -INFINITY) << e;
+            }
+            if (__builtin_amdgcn_ballot_w64(hidden != 0) != 0) {
+#pragma unroll
+                for (int i = 0; i < NV; i++) {
+                    const int row = i * KROWS + lane / NCK;     // lane 16 (row / 8) holds its bit
+                    if (__shfl(hidden, 16 * (row >> 3), 64) >> (row & 7) & 1) vr[i] = u32x4{0u, 0u, 0u, 0u};
+                }
+            }
         }
         // V to LDS (its readers below are this wave alone, so no barrier; a
         // wave's LDS operations are served in order)
@@ -461,13 +476,13 @@ __global__ void __launch_bounds__(64 * DEC_W) attn_decode_kernel(AttnDecodeArgs 
             *reinterpret_cast<u32x4*>(Vst + (size_t)row * D * 2 + (((lane % NCK) ^ vswz(row)) << 4)) = vr[i];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        load_stage(k0 + DEC_ST);          // (past the end: the share's first row, never used)
+        load_stage(k0 + DEC_ST);          // (past the end: the share's last row, never used)
         float sv[8];
         float mx = -INFINITY;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
             float v = sacc[e / 4][e % 4] * a.scale_log2;
-            if (a.mask) v += mk[e] * LOG2E;
+            if (a.mask) v = hidden >> e & 1 ? -INFINITY : v + ml[e];
             v = k0 + 8 * q4 + e < end ? v : -INFINITY;
             sv[e] = v;
             mx = fmaxf(mx, v);

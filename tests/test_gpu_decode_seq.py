@@ -73,3 +73,36 @@ def test_sequence_decode(shape, fmt, ctx, masked):
             outs[path].append(y)
     if B <= 2 and fmt == "int4" and cfg.group_size >= 64:     # the automatic path does not depend on timing
         assert torch.equal(*outs[0])
+
+
+@pytest.mark.parametrize("shape,fmt,ctx,pads", [
+    ("h896", "int4", (300,), (16,)), ("h1152", "int4", (500,), (301,)),          # one row, one share
+    ("h896", "int4", (511, 200), (64, 199)), ("h1152", "zeros", (2000, 1999, 700, 40), (1024, 1300, 3, 40)),
+    ("h256", "bf16", (900, 1023, 255), (900, 31, 255)), ("h896", "int8", (2303,), (2048,))])
+@pytest.mark.parametrize("stale", [0x7FC0, 0xFF80, 0x7F80])
+def test_hidden_and_unwritten_slots_may_hold_anything(shape, fmt, ctx, pads, stale):
+    """Slots hidden by the mask (the first pads[b] ones of a prompt padded on the
+    left) and slots past the context hold NaN or infinities in K and V, as memory
+    that was never written may."""
+    cfg, w, W, lay = layer(shape, fmt)
+    B, ctx = len(ctx), np.array(ctx, dtype=np.int32)
+    log(f"decode {shape} {fmt} ctx={ctx} pads={pads} stale={stale:#x}")
+    kb, vb = synth.kv_fill(cfg, B)
+    bits = synth.activations(cfg, synth.TID_X_DECODE, B)
+    mask = np.zeros((B, cfg.max_seq), dtype=np.float32)
+    ks, vs = kb.copy(), vb.copy()
+    for b in range(B):
+        mask[b, :pads[b]] = -np.inf if b % 2 == 0 else np.finfo(np.float32).min
+        for t in (ks, vs):
+            t[b, :, :pads[b]] = stale
+            t[b, :, ctx[b]:] = stale
+    yo, ko, vo = O.decode(w, cfg, O.bf16_to_f64(bits), ctx, O.bf16_to_f64(kb), O.bf16_to_f64(vb), ctx, W=W, mask=mask)
+    x, c = bits_to_torch_f32(bits), torch.from_numpy(ctx).cuda()
+    for path in (1, 0):
+        lay.set_decode_path(path)
+        k, v = (torch.from_numpy(t.view(np.int16).copy()).cuda() for t in (ks, vs))
+        y = torch.full_like(x, float("nan"))
+        lay.decode(x, c, c, int(ctx.max()), k, v, y, attn_mask=torch.from_numpy(mask).cuda())
+        torch.cuda.synchronize()
+        assert lay.error() == 0
+        assert_parity(y.cpu().numpy(), yo, f"y (path {path})")
