@@ -377,19 +377,26 @@ __global__ void __launch_bounds__(NW * 64) gemv_w4_kernel(GemvArgs a) {
     }
 }
 
+constexpr size_t kLdsMax = 160 * 1024;
+
+// LDS of a block: rows, zero operand, corrections, sums of squares; the wave
+// partials after them (a barrier less) unless only over the rows do two blocks
+// fit a CU (off_red 0)
+size_t lds_bytes(bool norm, bool zp, bool g32, int nw, int ct, int B, int K_pad, int ksplit, int& off_red) {
+    const int nkb = (K_pad / 64 + ksplit - 1) / ksplit;
+    const size_t rows = (size_t)B * (nkb * 64 + 8) * 2 + 128 + (size_t)nkb * GEMV_ROWS * (g32 ? 16 : zp ? 8 : 4) +
+                        (norm ? (size_t)B * nkb * 4 : 0);
+    const size_t red = (size_t)nw * ct * B * 32 * 4;
+    off_red = rows + red > 80 * 1024 ? 0 : (int)((rows + 15) / 16 * 16);
+    return off_red ? off_red + red : std::max(rows, red);
+}
+
 template <int EPI, bool NORM, bool ZP, bool G32, int WF, int NW, int CT>
 int launch_nw(const GemvArgs& a, hipStream_t stream) {
     const int KB = a.W.K_pad / 64;
-    const int kmax = (KB + a.ksplit - 1) / a.ksplit * 64;
-    // rows, zero operand, corrections, sums of squares; the wave partials after
-    // them (a barrier less) unless only over the rows do two blocks fit a CU
-    const size_t rows = (size_t)a.B * (kmax + 8) * 2 + 128 + (size_t)(kmax / 64) * GEMV_ROWS * (G32 ? 16 : ZP ? 8 : 4) +
-                        (NORM ? (size_t)a.B * (kmax / 64) * 4 : 0);
-    const size_t red = (size_t)NW * CT * a.B * 32 * 4;
     GemvArgs b = a;
-    b.off_red = rows + red > 80 * 1024 ? 0 : (int)((rows + 15) / 16 * 16);
-    const size_t smem = b.off_red ? b.off_red + red : std::max(rows, red);
-    if (smem > 160 * 1024) return -1;
+    const size_t smem = lds_bytes(NORM, ZP, G32, NW, CT, a.B, a.W.K_pad, a.ksplit, b.off_red);
+    if (smem > kLdsMax) return -1;
     if (NORM && (a.ksplit > 1 || a.B * ((KB + NW - 1) / NW) > NX * 8)) return -1;
     static LdsLimit lim;
     if (ensure_lds_limit(lim, (const void*)gemv_w4_kernel<EPI, NORM, ZP, G32, WF, NW, CT>, smem)) return -1;
@@ -429,15 +436,36 @@ int launch_zp(int epi, bool norm, const GemvArgs& a, hipStream_t stream) {
 // atomic adds, in any order.  `ordered`: the result must not depend on timing,
 // so at most two ranges (adds onto 0 commute); 16 waves on one tile then keep
 // the CUs busy, at 1 to 3 us more per layer (Llama-8B, one row, 300 keys:
-// 45.4 against 44.5 us; Qwen-0.5B 31.2 against 28.3).  More ranges if the
-// activation rows of one would not fit the LDS (128 KB).
+// 45.4 against 44.5 us; Qwen-0.5B 31.2 against 28.3).  More ranges until the
+// activation rows of one (at most 128 KB) and their corrections fit the LDS.
 void gemv_resid_plan(GemvArgs& a, bool ordered) {
     const int KB = a.W.K_pad / 64, pairs = a.W.N_dev / 64;
+    const bool zp = a.W.sz != nullptr, g32 = a.W.lgG == 5;
     a.ct = ordered ? 1 : 2;
     int ks = ordered ? (2 * pairs < a.num_cus && KB >= 32 ? 2 : 1)
                      : std::max(1, std::min((KB + 7) / 8, 2 * a.num_cus / pairs));
-    while ((long long)a.B * ((KB + ks - 1) / ks) * 64 * 2 > 128 * 1024 && ks < KB) ks++;
+    int off_red;
+    while (ks < KB && ((long long)a.B * ((KB + ks - 1) / ks) * 64 * 2 > 128 * 1024 ||
+                       lds_bytes(false, zp, g32, a.ct == 1 ? 16 : 8, a.ct, a.B, a.W.K_pad, ks, off_red) > kLdsMax))
+        ks++;
     a.ksplit = ks;
+}
+
+// (for the host tests: the k ranges and LDS bytes of a residual GEMV)
+extern "C" void w4_gemv_resid_plan(int B, int K_pad, int N_dev, int zp, int lgG, int ordered, int num_cus, int* ksplit,
+                                   uint64_t* lds) {
+    static const uint32_t word = 0;
+    GemvArgs a{};
+    a.B = B;
+    a.num_cus = num_cus;
+    a.W.K_pad = K_pad;
+    a.W.N_dev = N_dev;
+    a.W.lgG = lgG;
+    a.W.sz = zp ? &word : nullptr;
+    gemv_resid_plan(a, ordered != 0);
+    int off_red;
+    *ksplit = a.ksplit;
+    *lds = lds_bytes(false, zp != 0, lgG == 5, a.ct == 1 ? 16 : 8, a.ct, B, K_pad, a.ksplit, off_red);
 }
 
 bool gemv_norm_fits(int B, int K) { return B * ((K / 64 + 7) / 8) <= NX * 8; }

@@ -32,3 +32,29 @@ def test_gemv_blocks_cover_the_matrix(K, N, wf, ct):
         end = first + nbytes
     assert end == total
     assert nbytes <= 1 << 25 and nbytes < PAST_END
+
+
+def resid_plan(B_, K, N, zp=False, group=128, ordered=False, cus=256):
+    ks, lds = ctypes.c_int(), ctypes.c_uint64()
+    B._lib.w4_gemv_resid_plan(B_, K, N, int(zp), group.bit_length() - 1, int(ordered), cus, ctypes.byref(ks), ctypes.byref(lds))
+    return ks.value, lds.value
+
+
+@pytest.mark.parametrize("zp,group", [(False, 128), (True, 128), (False, 32), (True, 32)])
+def test_residual_gemvs_fit_the_lds(zp, group):
+    """Every width and depth that layer_create accepts gets k ranges whose rows and
+    corrections fit a CU's 160 KB, at every batch; ranges stay whole k tiles."""
+    for N in range(128, 16385, 128):
+        for K in (128, 2048, 14336, 28672, 32768, 40960, 53248, 57344, 61440, 65536):
+            for rows in range(1, 9):
+                ks, lds = resid_plan(rows, K, N, zp, group)
+                assert 1 <= ks <= K // 64 and lds <= 160 * 1024, (N, K, rows, ks, lds)
+
+
+def test_ordered_residual_gemvs_take_at_most_two_ranges():
+    """(Adds of two ranges onto 0 commute; one or two rows of the depths that the
+    persistent launch, whose place they take, can hold.)"""
+    for N in range(512, 16385, 128):
+        for K, rows in ((65536, 1), (40960, 1), (32768, 2), (32768, 1), (14336, 2), (512, 2)):
+            ks, lds = resid_plan(rows, K, N, ordered=True)
+            assert ks <= 2 and lds <= 160 * 1024, (N, K, rows, ks, lds)
