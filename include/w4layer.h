@@ -188,8 +188,9 @@ int kv_layout(const layer_config* cfg, int32_t batch, kv_desc* out);
 
 /* Bytes of device workspace a stage call needs: stage 0 prefill (batch 1,
  * T tokens), 1 prefill_kv (batch 1, T tokens, history up to max_ctx), 2
- * decode (batch sequences, context up to max_ctx).  Returns 0 for invalid
- * arguments. */
+ * decode (batch sequences, context up to max_ctx).  For stages 0 and 1 it does
+ * not decrease with T: a workspace for a longer prompt serves a shorter one.
+ * Returns 0 for invalid arguments. */
 size_t layer_workspace_size(layer_t layer, int32_t stage, int32_t batch, int32_t T, int32_t max_ctx);
 
 /* ---- the three stages (all device pointers; asynchronous on stream) ---- */

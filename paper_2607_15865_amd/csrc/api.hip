@@ -277,6 +277,8 @@ struct layer_s {
     DevBuf sync;
     int fused_blocks = 0, S_qkv = 1, S_o = 1, S_down = 1;   // persistent decode: blocks, k parts
     int num_cus = 256;
+    // [i]: the largest split-K partials of any prefill GEMM of up to 32 (i + 1) rows
+    std::vector<size_t> split_bytes;
     int* err = nullptr;
     unsigned long long* stamps = nullptr;
     int decode_path = 0;   // 0 auto, 1 separate kernels, 2 persistent
@@ -404,6 +406,22 @@ struct Carve {
 
 constexpr int kGemmCounters = 1024;     // split-K tiles of one GEMM (at most about one per CU)
 
+// The plan of a GEMM depends on its rows through their row tiles of 32, and fewer
+// rows can take more split partials than more rows do.  The workspace holds the
+// largest of up to T rows, so one made for a longer prompt serves a shorter one.
+void plan_splits(layer_s* L) {
+    for (int i = 0; i < (L->cfg.max_seq + 31) / 32; i++) {
+        size_t n = i ? L->split_bytes[i - 1] : 0;
+        bool more = false;
+        for (const DevLinear* W : {&L->qkv.d, &L->o.d, &L->gu.d, &L->down.d}) {
+            n = std::max(n, gemm_w4_plan(32 * (i + 1), *W, L->num_cus).part_bytes);
+            more |= gemm_w4_may_split(32 * (i + 1), *W, L->num_cus);
+        }
+        L->split_bytes.push_back(n);
+        if (!more) break;
+    }
+}
+
 struct PrefillWs {
     size_t xn1, q, attn, h, xn2, g, part, cnt, total;
     GemmPlan qkv, o, gu, down;
@@ -426,7 +444,8 @@ PrefillWs plan_prefill(const layer_s* L, int T, int hist) {
     w.xn2 = cv.take((size_t)T * c.hidden * 2);
     w.g = cv.take((size_t)T * L->F_pad * 2);
     // split-K partials of each GEMM and the attention chunk states, used one kernel at a time
-    w.part = cv.take(std::max({w.qkv.part_bytes, w.o.part_bytes, w.gu.part_bytes, w.down.part_bytes, w.at.part_bound}));
+    const size_t split = L->split_bytes[std::min((T - 1) / 32, (int)L->split_bytes.size() - 1)];
+    w.part = cv.take(std::max(split, w.at.part_bound));
     w.cnt = cv.take((size_t)4 * kGemmCounters * 4);   // split-K arrival counters, one set per GEMM
     w.total = cv.off;
     return w;
@@ -1107,6 +1126,7 @@ int layer_create(const layer_config* cfg, const layer_weights_host* w, layer_t* 
             }
         }
     }
+    plan_splits(L);
     *out = L;
     return W4_OK;
 }

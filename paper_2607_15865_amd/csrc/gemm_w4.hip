@@ -1,6 +1,9 @@
 // Prefill GEMM: launch plan and dispatch (the kernel: gemm_w4.h).
 #include "launch.h"
 
+// blocks of a launch that splits k, at most
+static long long max_split_blocks(int num_cus) { return num_cus * 11 / 5; }
+
 // Launch plan: the block shape and k split with the least estimated time.
 //
 // The estimate (in us) counts what a CU does: its rounds of 8 waves (one block
@@ -45,7 +48,7 @@ GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
             if (TM == 2 && WN == 2 && W.zeros && W.lgG == 5) continue;   // (would spill)
             for (int S : {1, 2, 3, 4, 6, 8}) {
                 const long long blocks = (long long)nrb * ncb * S;
-                if (S > 1 && (its < 2 * S * KG || blocks > num_cus * 11 / 5)) break;
+                if (S > 1 && (its < 2 * S * KG || blocks > max_split_blocks(num_cus))) break;
                 const double it = (its + S * KG - 1) / (S * KG) + 2;
                 const double us = (TM == 1 ? 0.61 : TM == 2 ? (W.wf == WF_F16 ? 0.78 : 0.88) : 1.33) * wf_cost;
                 const double usx = us + (WN == 2 ? x_cost * TM : 0.0);
@@ -63,6 +66,11 @@ GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
         }
     best.part_bytes = best.S > 1 ? (size_t)best.tiles * best.S * best.TM * 16 * best.WN * 64 * 8 : 0;
     return best;
+}
+
+bool gemm_w4_may_split(int M, const DevLinear& W, int num_cus) {
+    const long long tiles = (long long)((M + 127) / 128) * ((W.N_dev + 255) / 256);   // the fewest (TM 4, WN 4)
+    return 2 * tiles <= max_split_blocks(num_cus);
 }
 
 int launch_gemm_w4(int epi, const f16* X, int ldx, const DevLinear& W, const EpiArgs& ep, const GemmPlan& p,

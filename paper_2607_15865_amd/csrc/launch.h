@@ -50,6 +50,8 @@ struct GemmPlan {
     size_t part_bytes = 0;        // fp32 partial sums (S > 1)
 };
 GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus);
+// false: no plan of M rows or more splits k
+bool gemm_w4_may_split(int M, const DevLinear& W, int num_cus);
 // part: plan.part_bytes of workspace; cnt: plan.tiles arrival counters, zeroed
 // by an earlier launch on the stream (launch_rmsnorm) and used by this launch
 // alone.  Both are unused when plan.S == 1.

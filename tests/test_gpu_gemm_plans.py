@@ -55,3 +55,16 @@ def test_prefill_gemm_plan(shape, fmt, T):
     assert_parity(cache_values(k)[0][:, :T].transpose(1, 0, 2), ko, "new K")
     assert_parity(cache_values(v)[0][:, :T].transpose(1, 0, 2), vo, "new V")
     assert not np.any(cache_values(k)[0][:, T:]), "slots past the prompt are untouched"
+
+
+@pytest.mark.parametrize("fmt", ["int4", "bf16"])
+def test_workspace_does_not_shrink_with_longer_prompts(fmt):
+    """A shape whose k splits need more for 160 rows (16-bit: 32) than for some longer
+    prompts: a workspace for a longer prompt has to serve a shorter one."""
+    cfg = synth.LayerConfig("wide", 1024, 8, 2, 128, 7168, 128, 1e-6, 1e4, 1024, 8, 9)
+    if fmt == "bf16":
+        cfg = synth.replace(cfg, hidden=2048, n_heads=16, n_kv_heads=4, ffn=5632)
+    lay = binding.Layer(cfg, synth.make_layer(cfg, 0, **FORMATS[fmt]))
+    for stage, hist in ((0, 0), (1, 100)):
+        need = [binding.layer_workspace_size(lay.handle, stage, 1, T, hist) for T in range(1, 900)]
+        assert all(a <= b for a, b in zip(need, need[1:])), [T + 1 for T in range(898) if need[T] > need[T + 1]]
