@@ -441,6 +441,16 @@ int layer_debug_dequant(layer_t layer, int32_t which, float* out, void* stream);
  * kernels.  Errors: W4_EINVAL. */
 int layer_set_decode_path(layer_t layer, int32_t path);
 
+/* Launch plan of one prefill GEMM (testing; 0 q/k/v, 1 o_proj, 2 gate/up, 3
+ * down) instead of the one chosen by its rows: row_tile 32, 64 or 128 rows per
+ * block, waves 2 or 4 side by side (64 columns each), k_groups 1, 2 or 4 groups
+ * of them that share a block's k range, k_splits blocks along k.  row_tile 0
+ * restores the choice.  It counts for the sizes of layer_workspace_size too.
+ * Errors: W4_EINVAL; W4_EUNSUPPORTED (no such kernel for the layer's format, or
+ * more splits than the k range has steps of 128 per group). */
+int layer_set_gemm_plan(layer_t layer, int32_t gemm, int32_t row_tile, int32_t waves, int32_t k_groups,
+                        int32_t k_splits);
+
 /* Poll budget of the persistent decode path (testing): the number of polls
  * per thread and launch after which a wait for another block's data gives
  * up, raises W4_FLAG_WAIT_TIMEOUT and lets the launch run to its end (the

@@ -97,6 +97,7 @@ _SIG = {
     "kv_append": (ctypes.c_int, [ctypes.POINTER(kv_desc), _P, _P, _P, _P, _I, _I, _P, _P]),
     "layer_debug_dequant": (ctypes.c_int, [_P, _I, _P, _P]),
     "layer_set_decode_path": (ctypes.c_int, [_P, _I]),
+    "layer_set_gemm_plan": (ctypes.c_int, [_P, _I, _I, _I, _I, _I]),
     "layer_decode_phase_times": (ctypes.c_int, [_P, _P, _P]),
     "layer_debug_decode_stamps": (ctypes.c_int, [_P, _P, _I]),
     "layer_set_decode_trace": (ctypes.c_int, [_P, _I]),
@@ -337,6 +338,10 @@ def layer_set_decode_trace(handle, on: int) -> int:
 
 def layer_set_decode_spin_limit(handle, polls: int) -> int:
     return _lib.layer_set_decode_spin_limit(handle, polls)
+
+
+def layer_set_gemm_plan(handle, gemm: int, row_tile: int, waves: int, k_groups: int, k_splits: int) -> int:
+    return _lib.layer_set_gemm_plan(handle, gemm, row_tile, waves, k_groups, k_splits)
 
 
 def layer_set_decode_path(handle, path: int) -> int:

@@ -279,6 +279,8 @@ struct layer_s {
     int num_cus = 256;
     // [i]: the largest split-K partials of any prefill GEMM of up to 32 (i + 1) rows
     std::vector<size_t> split_bytes;
+    struct { int TM = 0, WN = 0, KG = 0, S = 0; } gemm_set[4];   // q/k/v, o_proj, gate/up, down: plans that a test
+                                                                 // chose (TM 0: automatic)
     int* err = nullptr;
     unsigned long long* stamps = nullptr;
     int decode_path = 0;   // 0 auto, 1 separate kernels, 2 persistent
@@ -422,6 +424,11 @@ void plan_splits(layer_s* L) {
     }
 }
 
+GemmPlan prefill_gemm_plan(const layer_s* L, int T, int gemm, const DevLinear& W) {
+    const auto& p = L->gemm_set[gemm];
+    return p.TM ? gemm_w4_plan_of(T, W, p.TM, p.WN, p.KG, p.S) : gemm_w4_plan(T, W, L->num_cus);
+}
+
 struct PrefillWs {
     size_t xn1, q, attn, h, xn2, g, part, cnt, total;
     GemmPlan qkv, o, gu, down;
@@ -432,10 +439,10 @@ PrefillWs plan_prefill(const layer_s* L, int T, int hist) {
     const size_t qd = (size_t)c.n_heads * c.head_dim;
     Carve cv;
     PrefillWs w;
-    w.qkv = gemm_w4_plan(T, L->qkv.d, L->num_cus);
-    w.o = gemm_w4_plan(T, L->o.d, L->num_cus);
-    w.gu = gemm_w4_plan(T, L->gu.d, L->num_cus);
-    w.down = gemm_w4_plan(T, L->down.d, L->num_cus);
+    w.qkv = prefill_gemm_plan(L, T, 0, L->qkv.d);
+    w.o = prefill_gemm_plan(L, T, 1, L->o.d);
+    w.gu = prefill_gemm_plan(L, T, 2, L->gu.d);
+    w.down = prefill_gemm_plan(L, T, 3, L->down.d);
     w.at = attn_prefill_plan(T, hist, c.n_heads, c.n_kv_heads, c.head_dim, L->num_cus);
     w.xn1 = cv.take((size_t)T * c.hidden * 2);
     w.q = cv.take((size_t)T * qd * 2);
@@ -445,7 +452,7 @@ PrefillWs plan_prefill(const layer_s* L, int T, int hist) {
     w.g = cv.take((size_t)T * L->F_pad * 2);
     // split-K partials of each GEMM and the attention chunk states, used one kernel at a time
     const size_t split = L->split_bytes[std::min((T - 1) / 32, (int)L->split_bytes.size() - 1)];
-    w.part = cv.take(std::max(split, w.at.part_bound));
+    w.part = cv.take(std::max({split, w.at.part_bound, w.qkv.part_bytes, w.o.part_bytes, w.gu.part_bytes, w.down.part_bytes}));
     w.cnt = cv.take((size_t)4 * kGemmCounters * 4);   // split-K arrival counters, one set per GEMM
     w.total = cv.off;
     return w;
@@ -1374,6 +1381,26 @@ int layer_set_decode_path(layer_t L, int32_t path) {
     if (!L) return fail(W4_EINVAL, "null layer");
     if (path < 0 || path > 2) return fail(W4_EINVAL, "path must be 0, 1 or 2");
     L->decode_path = path;
+    return W4_OK;
+}
+
+int layer_set_gemm_plan(layer_t L, int32_t gemm, int32_t row_tile, int32_t waves, int32_t k_groups, int32_t k_splits) {
+    if (!L) return fail(W4_EINVAL, "null layer");
+    if (gemm < 0 || gemm > 3) return fail(W4_EINVAL, "gemm must be 0..3");
+    auto& p = L->gemm_set[gemm];
+    if (row_tile == 0) {
+        p.TM = 0;
+    } else {
+        const DevLinear& W = (gemm == 0 ? L->qkv : gemm == 1 ? L->o : gemm == 2 ? L->gu : L->down).d;
+        if (row_tile % 32 || !gemm_w4_built(W, row_tile / 32, waves, k_groups))
+            return fail(W4_EUNSUPPORTED, "no GEMM of row tile %d, %d waves, %d k groups for this format", row_tile, waves, k_groups);
+        if (k_splits < 1 || (k_splits > 1 && k_splits * k_groups > W.K_pad / 128))
+            return fail(W4_EUNSUPPORTED, "k range of %d too short for %d splits", W.K_pad, k_splits);
+        p.TM = row_tile / 32;
+        p.WN = waves;
+        p.KG = k_groups;
+        p.S = k_splits;
+    }
     return W4_OK;
 }
 

@@ -4,6 +4,24 @@
 // blocks of a launch that splits k, at most
 static long long max_split_blocks(int num_cus) { return num_cus * 11 / 5; }
 
+bool gemm_w4_built(const DevLinear& W, int TM, int WN, int KG) {
+    if (TM == 4) return WN == 4 && KG == 1 && !W.zeros && W.lgG != 5 && W.wf == WF_INT4;
+    if (TM != 1 && TM != 2) return false;
+    if (W.wf == WF_F16 && TM == 2) return WN == 4 && KG == 1;
+    if (TM == 2 && WN == 2 && W.zeros && W.lgG == 5) return false;   // (would spill)
+    return (WN == 4 && (KG == 1 || KG == 2)) || (WN == 2 && KG == 4);
+}
+
+GemmPlan gemm_w4_plan_of(int M, const DevLinear& W, int TM, int WN, int KG, int S) {
+    GemmPlan p;
+    p.TM = TM; p.WN = WN; p.KG = KG; p.S = S;
+    p.nrb = (M + 32 * TM - 1) / (32 * TM);
+    p.ncb = (W.N_dev + 64 * WN - 1) / (64 * WN);
+    p.tiles = p.nrb * p.ncb;
+    p.part_bytes = S > 1 ? (size_t)p.tiles * S * TM * 16 * WN * 64 * 8 : 0;
+    return p;
+}
+
 // Launch plan: the block shape and k split with the least estimated time.
 //
 // The estimate (in us) counts what a CU does: its rounds of 8 waves (one block
@@ -30,22 +48,19 @@ static long long max_split_blocks(int num_cus) { return num_cus * 11 / 5; }
 // considered only from 0.75 tiles per CU on, 0.375 for k ranges of 12288 or more.
 GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
     const int its = W.K_pad / 128;
-    // the kernel variants that exist
-    const int tm_max = W.zeros || W.lgG == 5 || W.wf != WF_INT4 ? 2 : 4;
     const double wf_cost = W.wf == WF_F16 ? 1.6 : W.wf == WF_INT8 ? 1.1 : W.zeros ? 1.05 : 1.0;
     const double x_cost = W.wf == WF_INT8 ? 0.14 : 0.057;
     GemmPlan best;
     double best_cost = -1.0;
-    for (int TM = 1; TM <= tm_max; TM *= 2)
+    for (int TM = 1; TM <= 4; TM *= 2)
         for (int shape = 0; shape < 3; shape++) {
             const int WN = shape == 2 ? 2 : 4, KG = shape == 0 ? 1 : shape == 1 ? 2 : 4;
             const int nrb = (M + 32 * TM - 1) / (32 * TM), ncb = (W.N_dev + 64 * WN - 1) / (64 * WN);
-            if (W.wf == WF_F16 && TM == 2 && KG > 1) continue;
+            if (!gemm_w4_built(W, TM, WN, KG)) continue;
             if (TM == 4) {
                 const int need = W.K_pad >= 12288 ? num_cus * 3 / 2 : num_cus * 3;
-                if (KG > 1 || nrb * ncb * 4 < need) continue;
+                if (nrb * ncb * 4 < need) continue;
             }
-            if (TM == 2 && WN == 2 && W.zeros && W.lgG == 5) continue;   // (would spill)
             for (int S : {1, 2, 3, 4, 6, 8}) {
                 const long long blocks = (long long)nrb * ncb * S;
                 if (S > 1 && (its < 2 * S * KG || blocks > max_split_blocks(num_cus))) break;
@@ -59,12 +74,10 @@ GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus) {
                 if (KG > 1) cost += 0.4 * TM * WN;
                 if (best_cost < 0 || cost < best_cost) {
                     best_cost = cost;
-                    best.TM = TM; best.WN = WN; best.KG = KG; best.S = S;
-                    best.nrb = nrb; best.ncb = ncb; best.tiles = nrb * ncb;
+                    best = gemm_w4_plan_of(M, W, TM, WN, KG, S);
                 }
             }
         }
-    best.part_bytes = best.S > 1 ? (size_t)best.tiles * best.S * best.TM * 16 * best.WN * 64 * 8 : 0;
     return best;
 }
 

@@ -50,6 +50,9 @@ struct GemmPlan {
     size_t part_bytes = 0;        // fp32 partial sums (S > 1)
 };
 GemmPlan gemm_w4_plan(int M, const DevLinear& W, int num_cus);
+// the kernel variants that exist, and the plan of a given shape
+bool gemm_w4_built(const DevLinear& W, int TM, int WN, int KG);
+GemmPlan gemm_w4_plan_of(int M, const DevLinear& W, int TM, int WN, int KG, int S);
 // false: no plan of M rows or more splits k
 bool gemm_w4_may_split(int M, const DevLinear& W, int num_cus);
 // part: plan.part_bytes of workspace; cnt: plan.tiles arrival counters, zeroed

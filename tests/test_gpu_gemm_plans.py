@@ -1,5 +1,6 @@
-"""The prefill GEMM's block shapes and splits against the CPU oracle, at the
-sizes where they can go wrong: rows around the row tiles of 32, 64 and 128, k
+"""The prefill GEMM's block shapes and splits against the CPU oracle: every
+kernel variant with every split count on a small shape, and the planner's own
+choice at the sizes where they can go wrong: rows around the row tiles of 32, 64 and 128, k
 ranges with fewer iterations than k groups (hidden 256), with odd remainders
 over the k groups and splits (hidden 896 and 1152, FFN 688 and 4736), more rows
 than columns (blocks in row order), and every weight format.  The bound is the
@@ -68,3 +69,51 @@ def test_workspace_does_not_shrink_with_longer_prompts(fmt):
     for stage, hist in ((0, 0), (1, 100)):
         need = [binding.layer_workspace_size(lay.handle, stage, 1, T, hist) for T in range(1, 900)]
         assert all(a <= b for a, b in zip(need, need[1:])), [T + 1 for T in range(898) if need[T] > need[T + 1]]
+
+
+def variants():
+    """(format, group, row tile, waves, k groups) of the kernels that are built."""
+    for fmt, group in [(f, g) for f in ("int4", "zeros") for g in (32, 64, 128)] + [("int8", 128), ("bf16", 128)]:
+        for tm, wn, kg in [(tm, wn, kg) for tm in (32, 64) for wn, kg in ((4, 1), (4, 2), (2, 4))] + [(128, 4, 1)]:
+            if tm == 128 and (fmt != "int4" or group == 32):
+                continue
+            if tm == 64 and ((fmt == "bf16" and kg > 1) or (fmt == "zeros" and group == 32 and wn == 2)):
+                continue
+            yield fmt, group, tm, wn, kg
+
+
+@functools.lru_cache(maxsize=1)
+def variant_layer(fmt, group):
+    cfg = synth.replace(SHAPES["h1152"], group_size=group)        # 9 iterations of 128 k; down 8
+    w = synth.make_layer(cfg, 0, **FORMATS[fmt])
+    T = 300
+    bits = synth.activations(cfg, synth.TID_X_PREFILL, T)
+    return cfg, T, bits, O.prefill(w, cfg, O.bf16_to_f64(bits), np.arange(T), W=O.dequant_layer(w, cfg)), binding.Layer(cfg, w)
+
+
+@pytest.mark.parametrize("fmt,group,tm,wn,kg", variants())
+def test_every_gemm_variant_at_every_split(fmt, group, tm, wn, kg):
+    """All four GEMMs (three epilogues) on one block shape, for each split count the
+    planner knows (more than two iterations per k group are not needed here)."""
+    cfg, T, bits, (yo, ko, vo), lay = variant_layer(fmt, group)
+    lay.set_decode_path(1)
+    x = bits_to_torch_f32(bits)
+    for S in [s for s in (1, 2, 3, 4, 6, 8) if s == 1 or s * kg <= 8]:
+        log(f"prefill {fmt} group {group}: row tile {tm}, {wn} waves, {kg} k groups, {S} splits")
+        for gemm in range(4):
+            assert binding.layer_set_gemm_plan(lay.handle, gemm, tm, wn, kg, S) == 0, binding.layer_last_error()
+        k, v = lay.new_cache(1, 0)
+        y = torch.full_like(x, float("nan"))
+        lay.prefill(x, torch.arange(T, dtype=torch.int32, device="cuda"), k, v, y)
+        torch.cuda.synchronize()
+        assert lay.error() == 0
+        assert_parity(y.cpu().numpy(), yo, "y")
+        assert_parity(cache_values(k)[0][:, :T].transpose(1, 0, 2), ko, "new K")
+        assert_parity(cache_values(v)[0][:, :T].transpose(1, 0, 2), vo, "new V")
+
+
+def test_gemm_plan_refuses_what_is_not_built():
+    lay = variant_layer("zeros", 32)[4]
+    for plan in ((128, 4, 1, 1), (64, 2, 4, 1), (32, 2, 2, 1), (33, 4, 1, 1), (32, 4, 1, 0), (32, 4, 2, 5)):
+        assert binding.layer_set_gemm_plan(lay.handle, 0, *plan) == binding.W4_EUNSUPPORTED, plan
+    assert binding.layer_set_gemm_plan(lay.handle, 4, 32, 4, 1, 1) == binding.W4_EINVAL
