@@ -223,7 +223,6 @@ void repack_cols_x(const std::vector<ColSrc>& cols, int K_pad, int wf, Repacked&
         for (int g = 0; g < KG; g++) {
             const size_t gi = (size_t)g * N_dev + nd;
             R.scales[gi] = sc;
-            R.ratios[gi] = 1.0f;
             if (wf == 1) {
                 R.zeros[gi] = z;
                 R.sz[gi] = (uint32_t)sc | ((uint32_t)z << 16);
@@ -309,7 +308,7 @@ int build_linear(DevLinearOwned& out, const std::vector<ColSrc>& cols, int K, in
     Repacked R;
     R.qw.resize((size_t)N_dev * K_pad / 8 << wf);
     R.scales.resize((size_t)N_dev * KG);
-    R.ratios.resize((size_t)N_dev * KG);
+    if (wf == WF_INT4) R.ratios.resize((size_t)N_dev * KG);
     if (has_zeros) {
         R.zeros.resize((size_t)N_dev * KG);
         R.sz.resize((size_t)N_dev * KG);

@@ -17,8 +17,8 @@
 //   Tile index: nb * (K_pad / 64) + kb (column strips contiguous along k).
 //   Group parameters are group-major, so the 32 lanes of a tile read one
 //   contiguous run: scales fp16 [K_pad / G][N_dev]; ratios for the prefill
-//   GEMM fp32 [K_pad / G][N_dev] with ratio[g][n] = s[g-1][n] / s[g][n]
-//   (g >= 1).  Zero points (optional): uint8 [K_pad / G][N_dev], and the same
+//   GEMM (4-bit weights) fp32 [K_pad / G][N_dev] with
+//   ratio[g][n] = s[g-1][n] / s[g][n] (g >= 1).  Zero points (optional): uint8 [K_pad / G][N_dev], and the same
 //   again packed with the scale bits as uint32 (scale | zero << 16) for the
 //   decode GEMV.
 //
@@ -286,7 +286,7 @@ enum WeightFormat { WF_INT4 = 0, WF_INT8 = 1, WF_F16 = 2 };
 struct DevLinear {
     const uint32_t* qw;      // tiles
     const uint16_t* scales;  // fp16 bits [KG][N_dev]
-    const float* ratios;     // [KG][N_dev]
+    const float* ratios;     // [KG][N_dev]; null for the 8- and 16-bit formats
     const uint8_t* zeros;    // [KG][N_dev] or null
     const uint32_t* sz;      // scale bits | zero << 16, [KG][N_dev]; null without zeros
     int K, N;                // logical

@@ -106,7 +106,6 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
     constexpr int BM = 32 * TM;
     constexpr int XL = BM / (4 * WN);                   // X loads (1 KB) per wave and iteration
     constexpr int NH = GT == 0 ? 2 : 1;                 // group parameters per tile
-    constexpr int RS = 8;                               // weight tile slots: two iterations
     constexpr bool XREG = TM < 4 && !(TM == 2 && WF == WF_F16);
     static_assert(XREG || (WN == 4 && KG == 1), "X straight to LDS: four waves side by side");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -363,7 +362,7 @@ gemm_w4_kernel(const f16* __restrict__ X, int ldx, DevLinear W, EpiArgs ep, Gemm
     const float sl0 = FS ? 1.0f : (float)__builtin_bit_cast(f16, W.scales[(size_t)glast * W.N_dev + col0]);
     const float sl1 = FS ? 1.0f : (float)__builtin_bit_cast(f16, W.scales[(size_t)glast * W.N_dev + col1]);
     // q/k/v: the column pair (nt0 * 32 + c, + 32) holds dims dim0 and dim1 of
-    // head `head` of q (kind 0), k (1) or v (2) (see epi_qkv_pair)
+    // head `head` of q (kind 0), k (1) or v (2): a RoPE pair (rope_block)
     int kind = 0, head = 0, dim0 = 0, dim1 = 0;
     if (EPI == EPI_QKV) {
         const int d = ep.head_dim, qd = ep.nq * d, kd = ep.nkv * d;

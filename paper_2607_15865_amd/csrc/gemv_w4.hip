@@ -405,13 +405,16 @@ int launch_nw(const GemvArgs& a, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// 8 waves on a tile pair; where that leaves fewer blocks than CUs, 16 waves,
-// and for the residual products on one tile (a.ksplit was chosen for that,
-// gemv_ksplit).
+// 8 waves on a tile pair; where that leaves fewer blocks than CUs, 16 waves.
+// Residual products in their ordered form (gemv_resid_plan), which only layers
+// that the persistent launch could serve take: 16 waves on one tile.
 template <int EPI, bool NORM, bool ZP, bool G32, int WF>
 int launch_t(const GemvArgs& a, hipStream_t stream) {
     if constexpr (EPI == EPI_RESID) {
-        if (a.ct == 1) return launch_nw<EPI, NORM, ZP, G32, WF, 16, 1>(a, stream);
+        if constexpr (WF == WF_INT4 && !ZP && !G32) {
+            if (a.ct == 1) return launch_nw<EPI, NORM, ZP, G32, WF, 16, 1>(a, stream);
+        }
+        if (a.ct != 2) return -1;
     } else {
         if (a.W.N_dev / 64 <= a.num_cus) return launch_nw<EPI, NORM, ZP, G32, WF, 16, 2>(a, stream);
     }

@@ -1,46 +1,6 @@
-// Kernel launchers (internal) and the q/k/v epilogue shared by the GEMM and
-// the GEMV.
+// Kernel launchers (internal).
 #pragma once
 #include "common.h"
-
-// q/k/v epilogue for one row and one RoPE pair of device columns.
-// n_base: device column of the first tile of the pair (multiple of 64);
-// c: column inside the tile; v0, v1: sums of columns n_base + c and
-// n_base + 32 + c, which hold dims i and i + d/2 of the same head.
-// RoPE (Sec. 3.1 Listing 1, table of Sec. 4.6.2) is applied to q and k; the
-// results are rounded to bf16 and written to the q buffer or the cache slot.
-__device__ __forceinline__ void epi_qkv_pair(const EpiArgs& ep, int row, int n_base, int c,
-                                             float v0, float v1, int slot, int seq) {
-    const int d = ep.head_dim;
-    const int qd = ep.nq * d, kd = ep.nkv * d;
-    int n = n_base;
-    int kind, head;
-    if (n < qd) { kind = 0; head = n / d; n -= head * d; }
-    else if (n < qd + kd) { kind = 1; n -= qd; head = n / d; n -= head * d; }
-    else { kind = 2; n -= qd + kd; head = n / d; n -= head * d; }
-    const int p0 = n / 32;
-    const int dim0 = 32 * rope_block(p0, d) + c;
-    const int dim1 = 32 * rope_block(p0 + 1, d) + c;
-    float o0 = v0, o1 = v1;
-    if (kind < 2) {
-        const int pos = ep.pos[row];
-        const float cs = ep.rope_cos[(size_t)pos * (d / 2) + dim0];
-        const float sn = ep.rope_sin[(size_t)pos * (d / 2) + dim0];
-        o0 = v0 * cs - v1 * sn;
-        o1 = v1 * cs + v0 * sn;
-    }
-    const uint16_t b0 = bf16_bits_rne(o0), b1 = bf16_bits_rne(o1);
-    if (kind == 0) {
-        uint16_t* q = ep.q_out + ((size_t)row * ep.nq + head) * d;
-        q[dim0] = b0;
-        q[dim1] = b1;
-    } else {
-        uint16_t* cache = (kind == 1) ? ep.k_cache : ep.v_cache;
-        uint16_t* p = cache + (size_t)seq * ep.cache_stride_b + (size_t)head * ep.cache_stride_h + (size_t)slot * d;
-        p[dim0] = b0;
-        p[dim1] = b1;
-    }
-}
 
 // Prefill GEMM launch plan: row tile (32 * TM rows), block shape (WN waves
 // side by side, 64 columns each; KG groups of them that share out the block's
