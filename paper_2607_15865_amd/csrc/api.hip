@@ -568,12 +568,12 @@ FusedPlan plan_fused(const layer_s* L, int B, int max_ctx, bool query_device) {
     return p;
 }
 
-// Tag of a launch whose blocks hand data to each other through workspace
-// words (the persistent decode, the split-K arrival counters): unique for
-// 2^32 - 1 launches in the process and never 0 (a zeroed workspace holds no
-// valid word).  The sequence starts at a point mixed from the clock and the
-// process id, so a word that another process left in reused device memory
-// matches a current tag only by chance (about 2^-32 per word).
+// Tag of a persistent decode launch, whose blocks hand data to each other
+// through tagged workspace words that nothing clears: unique for 2^32 - 1
+// launches in the process and never 0 (a zeroed workspace holds no valid word).
+// The sequence starts at a point mixed from the clock and the process id, so a
+// word that another process left in reused device memory matches a current tag
+// only by chance (about 2^-32 per word).
 uint32_t epoch_start() {
     uint64_t z = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^
                  ((uint64_t)getpid() << 32);
@@ -683,7 +683,7 @@ int launch_fused(layer_s* L, const FusedPlan& fp, const float* x, const int32_t*
 }
 
 // The decode as a sequence of kernels (GEMVs on up to 8 rows, split-KV
-// attention, chunk merge).  shared: the B rows are consecutive tokens of one
+// attention that merges its shares itself).  shared: the B rows are consecutive tokens of one
 // sequence with one cache (prefill / prefill_kv of at most 8 tokens), row b
 // at context ctx_base + b: the q/k/v GEMV writes every row's new key and
 // value before the attention kernel reads the cache.  ordered: the result does

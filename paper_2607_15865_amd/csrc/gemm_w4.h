@@ -24,25 +24,27 @@
 // the partial sums in memory that a k split over blocks costs.  Shapes
 // (WN, KG): (4, 1), (4, 2), (2, 4).
 //
-// Pipeline, per iteration of BK = 128 k (two 64-k weight tiles per column):
-// at its start a block requests everything the next iteration needs, and
-// the barrier at its end (whose workgroup release waits for the block's
-// outstanding loads) makes it visible:
-//   * the X tile (BM x 128 fp16) goes straight from memory to LDS with
-//     direct-to-LDS loads (one 1 KB wave load per 4 rows), so it costs no
-//     registers; rows are 256 bytes without padding, and the 16-byte chunk c
-//     of row r is stored at chunk c ^ (r & 15), so the A-fragment reads of
-//     16 consecutive rows hit 16 different bank groups;
-//   * each wave loads its 4 weight tiles (1 KB each, one 16-byte load per
-//     lane) into the free half of a register ring of 8 tile slots;
-//   * inside the iteration the A fragments (LDS) and B fragments of step
-//     t + 1 are prepared while the MFMAs of step t run;
-//   * the scale ratio that the accumulators take at the end of an iteration
-//     (the next iteration's first group) was requested an iteration earlier,
-//     so no instruction of an iteration waits for that iteration's loads.
-// Every load is issued unconditionally with clamped addresses (X rows past M
-// read row M - 1; their outputs are dropped).  K_pad is a multiple of 128, so
-// every k range holds whole iterations.
+// Pipeline, per iteration of BK = 128 k (two 64-k weight tiles per column).
+// The X tile (BM x 128 fp16) lies in LDS, two buffers in turn; its rows are 256
+// bytes without padding, and the 16-byte chunk c of row r is stored at chunk
+// c ^ (r & 15), so the A-fragment reads of 16 consecutive rows hit 16 different
+// bank groups.  Each wave holds its weight tiles (4 per iteration; 1 KB with 4
+// bits, one 16-byte load per lane) in registers.  Two forms:
+//   * row tiles of 32 and 64 (XREG): X and weights are requested P = 2 to 4
+//     iterations ahead into P register stages; at the end of an iteration the
+//     next one's X goes from its stage to LDS, and the barrier waits for
+//     LDS writes only, so the deeper loads stay in flight;
+//   * row tiles of 128, and of 64 with 16-bit weights: X goes straight from
+//     memory to LDS (direct-to-LDS loads, 1 KB per 4 rows, no registers), one
+//     iteration ahead, with the weights; the barrier's workgroup release waits
+//     for the block's outstanding loads.  The scale ratio that the accumulators
+//     take at the end of an iteration (the next one's first group) is
+//     requested two iterations ahead.
+// In both, the A fragments (LDS) and B fragments of step t + 1 are prepared
+// while the MFMAs of step t run, and no instruction of an iteration waits for
+// that iteration's loads.  Every load is issued unconditionally with clamped
+// addresses (X rows past M read row M - 1; their outputs are dropped).  K_pad
+// is a multiple of 128, so every k range holds whole iterations.
 //
 // Split K: with S > 1 the k tiles are cut into S ranges, one block each.
 // Every block stores its fp32 partial tile, and the last block of a tile to

@@ -1,11 +1,11 @@
 """Stage calls that share one layer handle.
 
 The handle holds no device state that a prefill call changes: the split-K
-arrival counters of the GEMMs live in the caller's workspace as tagged words
-that need no clearing.  So prefill calls in flight together on two streams,
+arrival counters of the GEMMs live in the caller's workspace, and the first
+launch of a call clears them.  So prefill calls in flight together on two streams,
 each with its own workspace, caches and output, give the same bits as the
 same calls made one after another; and a workspace that a decode call left
-full of its own tagged words serves a prefill_kv call without clearing."""
+full of its own tagged words serves a prefill_kv call as it is."""
 import numpy as np
 import pytest
 import torch
