@@ -380,6 +380,13 @@ int check_device() {
     return 0;
 }
 
+int load_kernels() {
+    if (load_gemm_w4_qkv() || load_gemm_w4_resid() || load_gemm_w4_swiglu() || load_gemv_w4() || load_attention() ||
+        load_misc() || load_decode_fused() || load_lm())
+        return fail(W4_EHIP, "kernels not loaded: %s", hipGetErrorString(hipGetLastError()));
+    return W4_OK;
+}
+
 // Device address of `scratch` on the current device, looked up once per
 // device (with that device current) and kept.
 int scratch_setup() {
@@ -1003,6 +1010,7 @@ int layer_create(const layer_config* cfg, const layer_weights_host* w, layer_t* 
     if (!w->attn_norm || !w->mlp_norm) return fail(W4_EINVAL, "null norm weight");
     if ((rc = check_device())) return rc;
     if ((rc = scratch_setup())) return rc;
+    if ((rc = load_kernels())) return rc;
     const bool zq = w->q.zeros || w->k.zeros || w->v.zeros || w->o.zeros || w->gate.zeros || w->up.zeros || w->down.zeros;
     if (zq && !(w->q.zeros && w->k.zeros && w->v.zeros && w->o.zeros && w->gate.zeros && w->up.zeros && w->down.zeros))
         return fail(W4_EINVAL, "zero points must be given for all seven linears or for none");
@@ -1493,13 +1501,15 @@ int lm_create(const lm_config* cfg, const lm_weights_host* w, lm_t* out) {
         for (size_t i = 0; i < (size_t)KG * V; i++)
             if (w->head.zeros[i] > 15) return fail(W4_EINVAL, "zero point above 15 in the LM head");
 
+    int rc;
+    if ((rc = load_kernels())) return rc;
     lm_s* M = new lm_s();
     M->cfg = c;
     (void)hipGetDevice(&M->device);
     const HostLin hl{w->head.qweight, w->head.scales, w->head.zeros, H, V};
     std::vector<ColSrc> cols(V);
     for (int n = 0; n < V; n++) cols[n] = ColSrc{&hl, n};
-    int rc = build_linear(M->head, cols, H, H, G, w->head.zeros != nullptr);
+    rc = build_linear(M->head, cols, H, H, G, w->head.zeros != nullptr);
     if (!rc) rc = upload(M->embed, w->embed, (size_t)V * H * 2);
     if (!rc) rc = upload(M->final_norm, w->final_norm, (size_t)H * 2);
     if (!rc) {

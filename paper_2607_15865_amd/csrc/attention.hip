@@ -758,3 +758,5 @@ int launch_attn_decode(const AttnDecodeArgs& a, hipStream_t stream) {
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
+
+int load_attention() { return load_code((const void*)attn_decode_kernel<128>); }

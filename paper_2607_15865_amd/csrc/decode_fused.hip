@@ -887,3 +887,5 @@ int launch_decode_fused(const DecodeFusedArgs& a, hipStream_t stream) {
     if (a.d == 64) return a.B <= 1 ? launch_t<64, 1>(a, stream) : launch_t<64, 4>(a, stream);
     return -1;
 }
+
+int load_decode_fused() { return load_code((const void*)decode_fused_kernel<128, 1>); }

@@ -6,3 +6,5 @@ int launch_gemm_w4_qkv(const f16* X, int ldx, const DevLinear& W, const EpiArgs&
                       hipStream_t stream) {
     return launch_epi<EPI_QKV>(p, X, ldx, W, ep, gs, stream);
 }
+
+int load_gemm_w4_qkv() { return load_code((const void*)gemm_w4_kernel<EPI_QKV, 1, 2, false, WF_INT4, 4, 1>); }

@@ -488,3 +488,5 @@ int launch_gemv_w4(int epi, bool norm, const GemvArgs& a, hipStream_t stream) {
     if (a.W.sz) return g32 ? launch_zp<true, true>(epi, norm, a, stream) : launch_zp<true, false>(epi, norm, a, stream);
     return g32 ? launch_zp<false, true>(epi, norm, a, stream) : launch_zp<false, false>(epi, norm, a, stream);
 }
+
+int load_gemv_w4() { return load_code((const void*)gemv_w4_kernel<EPI_QKV, true, false, false, WF_INT4, 8, 2>); }

@@ -127,3 +127,13 @@ int launch_kv_append(uint16_t* k_cache, uint16_t* v_cache, const uint16_t* k_new
 
 int launch_debug_dequant(const DevLinear& W, const int32_t* col_map, int K, int N, float* out,
                          hipStream_t stream);
+
+// load_code of each source
+int load_gemm_w4_qkv();
+int load_gemm_w4_resid();
+int load_gemm_w4_swiglu();
+int load_gemv_w4();
+int load_attention();
+int load_misc();
+int load_decode_fused();
+int load_lm();

@@ -145,3 +145,5 @@ int launch_pick_guard(const int* const* flags, int n, int32_t* next, int B, hipS
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
+
+int load_lm() { return load_code((const void*)embed_kernel); }

@@ -143,3 +143,5 @@ int launch_debug_dequant(const DevLinear& W, const int32_t* col_map, int K, int 
     hipLaunchKernelGGL(debug_dequant_kernel, dim3(blocks), dim3(256), 0, stream, W, col_map, K, N, out);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
+
+int load_misc() { return load_code((const void*)kv_append_kernel); }
