@@ -432,7 +432,9 @@ int layer_debug_dequant(layer_t layer, int32_t which, float* out, void* stream);
  * deterministic, and so is the sequence where the automatic choice takes it in
  * the persistent launch's place; otherwise the sequence adds k-split partials
  * with atomics in any order.  With 2, a decode call the persistent
- * path cannot serve fails with W4_EUNSUPPORTED.  The decode kernels also
+ * path cannot serve fails with W4_EUNSUPPORTED; so does a decode call under
+ * stream capture (replays of the launch would share its tag), where the
+ * automatic choice is the sequence.  The decode kernels also
  * serve layer_prefill / layer_prefill_kv calls of a few tokens, the tokens
  * as rows of one sequence sharing its cache (row t also attends to the new
  * keys of rows before it): with path 0 up to 8 tokens (up to 2 as the

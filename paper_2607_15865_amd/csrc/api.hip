@@ -825,6 +825,18 @@ bool prefer_seq(const layer_s* L, int B, int max_ctx) {
     return L->decode_path == 0 && L->cfg.hidden >= 512 && (B == 2 || max_ctx < 512);
 }
 
+// A captured persistent launch would carry the same tag in every replay, and a
+// replay's blocks would take the words of the one before for their inputs.  So
+// calls under stream capture do without it.
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return s != hipStreamCaptureStatusNone;
+}
+
 // Prefill / prefill_kv of a few tokens runs on the decode kernels, the tokens
 // as rows sharing one cache: up to 2 tokens (4 with decode path 2) as one
 // persistent launch or the decode kernel sequence (prefer_seq), up to 8 (decode
@@ -854,8 +866,10 @@ int run_prefill(layer_s* L, const float* x, const int32_t* pos, int T, int hist,
     if ((long long)hist + T > c.max_seq) return fail(W4_ECAPACITY, "hist_len + T = %lld exceeds max_seq %d", (long long)hist + T, c.max_seq);
     hipStream_t st = (hipStream_t)stream_;
     const int stage = hist > 0 ? 1 : 0;
-    const FusedPlan fp = small_prefill_plan(L, T, hist);
-    const bool seq = fp.ok && prefer_seq(L, T, hist + T - 1) && ws_bytes >= plan_decode(L, T, hist + T - 1).total;
+    FusedPlan fp = small_prefill_plan(L, T, hist);
+    const bool cap = fp.ok && capturing(st);
+    if (cap && L->decode_path == 2) fp.ok = false;         // (the prefill kernels)
+    const bool seq = fp.ok && (cap || (prefer_seq(L, T, hist + T - 1) && ws_bytes >= plan_decode(L, T, hist + T - 1).total));
     if (fp.ok && !seq) {
         if (ws_bytes < fp.total) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, fp.total);
         int rc;
@@ -930,7 +944,8 @@ int decode_run(layer_s* L, const float* x, const int32_t* pos, const int32_t* ct
                const float* attn_mask, int B, void* kc, void* vc, float* y, void* ws, size_t ws_bytes,
                hipStream_t st, int ps_stage) {
     const FusedPlan fp = decode_fused_choice(L, B, max_ctx);
-    const bool seq = fp.ok && prefer_seq(L, B, max_ctx) && ws_bytes >= plan_decode(L, B, max_ctx).total;
+    const bool cap = fp.ok && capturing(st);
+    const bool seq = fp.ok && (cap || (prefer_seq(L, B, max_ctx) && ws_bytes >= plan_decode(L, B, max_ctx).total));
     if (fp.ok && !seq) {
         if (ws_bytes < fp.total) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, fp.total);
         int rc;
@@ -949,10 +964,10 @@ FusedPlan decode_fused_choice(layer_s* L, int B, int max_ctx) {
     return plan_fused(L, B, max_ctx, true);
 }
 
-// Every check of a decode call of B rows up to context max_ctx that does not
-// look at pointers, so a stack or model step can check all its layers
+// Every check of a decode call of B rows up to context max_ctx (on stream *st)
+// that does not look at pointers, so a stack or model step can check all its layers
 // before it enqueues the first kernel.
-int decode_check(layer_s* L, int B, int max_ctx) {
+int decode_check(layer_s* L, int B, int max_ctx, const hipStream_t* st = nullptr) {
     const layer_config& c = L->cfg;
     if (B < 1 || max_ctx < 0) return fail(W4_EINVAL, "B must be >= 1 and max_ctx >= 0");
     if (B > c.max_batch) return fail(W4_ECAPACITY, "B = %d exceeds max_batch %d", B, c.max_batch);
@@ -961,6 +976,8 @@ int decode_check(layer_s* L, int B, int max_ctx) {
         return fail(W4_ECAPACITY, "max_ctx + 1 = %lld exceeds max_seq %d", (long long)max_ctx + 1, c.max_seq);
     if (L->decode_path == 2 && !plan_fused(L, B, max_ctx, true).ok)
         return fail(W4_EUNSUPPORTED, "persistent decode not possible for this shape/batch");
+    if (L->decode_path == 2 && st && capturing(*st))
+        return fail(W4_EUNSUPPORTED, "the persistent decode cannot run under stream capture");
     return W4_OK;
 }
 
@@ -1209,7 +1226,8 @@ int layer_decode(layer_t L, const float* x, const int32_t* pos, const int32_t* c
     if (!x || !pos || !ctx_lens || !kc || !vc || !y || !ws) return fail(W4_EINVAL, "null pointer argument");
     if ((const void*)x == (const void*)y) return fail(W4_EINVAL, "x and y must not alias");
     int rc;
-    if ((rc = decode_check(L, B, max_ctx))) return rc;
+    const hipStream_t st = (hipStream_t)stream;
+    if ((rc = decode_check(L, B, max_ctx, &st))) return rc;
     return decode_run(L, x, pos, ctx_lens, max_ctx, attn_mask, B, kc, vc, y, ws, ws_bytes, (hipStream_t)stream, 2);
 }
 
@@ -1219,7 +1237,8 @@ int layer_decode_noalloc(layer_t L, const float* x, const int32_t* pos, const in
     if (!x || !pos || !ctx_lens || !kc || !vc || !y) return fail(W4_EINVAL, "null pointer argument");
     if ((const void*)x == (const void*)y) return fail(W4_EINVAL, "x and y must not alias");
     int rc;
-    if ((rc = decode_check(L, B, max_ctx))) return rc;
+    const hipStream_t st = (hipStream_t)stream;
+    if ((rc = decode_check(L, B, max_ctx, &st))) return rc;
     if (L->device < 0 || L->device >= kMaxDevices || !g_scratch[L->device])
         return fail(W4_EHIP, "scratch array not set up on device %d", L->device);
     const size_t need = layer_workspace_size(L, 2, B, 1, max_ctx);
@@ -1327,8 +1346,9 @@ int stack_decode(const layer_t* layers, int32_t n, const float* x, const int32_t
     if ((rc = check_stack(layers, n))) return rc;
     if (!x || !y || !ws || !k_caches || !v_caches) return fail(W4_EINVAL, "null pointer argument");
     if ((const void*)x == (const void*)y) return fail(W4_EINVAL, "x and y must not alias");
+    const hipStream_t st = (hipStream_t)stream;
     for (int i = 0; i < n; i++)
-        if ((rc = decode_check(layers[i], B, max_ctx))) return rc;
+        if ((rc = decode_check(layers[i], B, max_ctx, &st))) return rc;
     const size_t need = stack_workspace_size(layers, n, 2, B, 1, max_ctx);
     if (need == 0 || ws_bytes < need) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
     const size_t act = stack_act_offset(need - 2 * (size_t)B * layers[0]->cfg.hidden * sizeof(float));
@@ -1596,10 +1616,10 @@ namespace {
 size_t model_act_bytes(int B, int H) { return ((size_t)B * H * 4 + 255) / 256 * 256; }
 // every layer can decode B sequences at a context up to max_ctx (the checks
 // of a decode call: capacity, the batch limit, a forced persistent path)
-int model_check(const layer_t* layers, int n, int B, int max_ctx) {
+int model_check(const layer_t* layers, int n, int B, int max_ctx, const hipStream_t* st = nullptr) {
     for (int i = 0; i < n; i++) {
         if (!layers[i]) return fail(W4_EINVAL, "null layer %d", i);
-        const int rc = decode_check(layers[i], B, max_ctx);
+        const int rc = decode_check(layers[i], B, max_ctx, st);
         if (rc) return rc;
     }
     return W4_OK;
@@ -1628,7 +1648,8 @@ int model_decode_greedy(const layer_t* layers, int32_t n_layers, lm_t lm, const 
     if (B < 1 || max_ctx < 0) return fail(W4_EINVAL, "B must be >= 1 and max_ctx >= 0");
     if (B > lm->cfg.max_batch) return fail(W4_ECAPACITY, "B %d > the LM ends' max_batch %d", B, lm->cfg.max_batch);
     int rc;
-    if ((rc = model_check(layers, n_layers, B, max_ctx))) return rc;
+    const hipStream_t st = (hipStream_t)stream;
+    if ((rc = model_check(layers, n_layers, B, max_ctx, &st))) return rc;
     const size_t need = model_decode_workspace_size(layers, n_layers, lm, B, max_ctx);
     if (need == 0) return fail(W4_ECAPACITY, "B or max_ctx outside what the layers hold");
     if (!ws || ws_bytes < need) return fail(W4_EWORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);

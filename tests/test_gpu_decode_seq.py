@@ -106,3 +106,55 @@ def test_hidden_and_unwritten_slots_may_hold_anything(shape, fmt, ctx, pads, sta
         torch.cuda.synchronize()
         assert lay.error() == 0
         assert_parity(y.cpu().numpy(), yo, f"y (path {path})")
+
+
+@pytest.mark.parametrize("rows,tokens", [(1, 0), (2, 0), (0, 1), (0, 2)])
+def test_captured_calls_replay(rows, tokens):
+    """A decode of 1 or 2 rows over 1000 keys, or a prefill_kv of 1 or 2 tokens,
+    captured once and replayed on new inputs, with eager calls between the
+    replays: every replay gives the eager result (the persistent launch, which
+    such calls take otherwise, hands its data over under a tag that a replay
+    would repeat).  Asking for it under capture is refused."""
+    cfg, w, W, lay = layer("h896", "int4")
+    lay.set_decode_path(0)
+    n, ctx = rows or tokens, 1000
+    log(f"capture: {rows} rows, {tokens} tokens")
+    ws = torch.empty(max(binding.layer_workspace_size(lay.handle, 2, n, 1, ctx), binding.layer_workspace_size(lay.handle, 1, 1, n, ctx)),
+                     dtype=torch.uint8, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.zeros((n, cfg.hidden), device="cuda")
+    y = torch.zeros_like(x)
+    shape = (rows or 1, cfg.n_kv_heads, cfg.max_seq, cfg.head_dim)
+    k, v = (torch.zeros(shape, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    c = torch.full((n,), ctx, dtype=torch.int32, device="cuda")
+    pos = torch.arange(ctx, ctx + n, dtype=torch.int32, device="cuda")
+
+    def call(out, k, v):
+        if rows:
+            return binding.layer_decode(lay.handle, x, c, c, ctx, None, rows, k, v, out, ws, ws.numel())
+        return binding.layer_prefill_kv(lay.handle, x, pos, tokens, ctx, k, v, out, ws, ws.numel())
+
+    binding.check(call(y, k, v))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = call(y, k, v)
+        if rows:
+            lay.set_decode_path(2)
+            refused = call(y, k, v)
+            lay.set_decode_path(0)
+    binding.check(captured)
+    assert not rows or refused == binding.W4_EUNSUPPORTED
+    for _ in range(4):
+        x.normal_(generator=gen)
+        k.normal_(generator=gen)
+        v.normal_(generator=gen)
+        k2, v2, ref = k.clone(), v.clone(), torch.zeros_like(y)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = y.clone()
+        binding.check(call(ref, k2, v2))
+        torch.cuda.synchronize()
+        assert_parity(got.cpu().numpy(), ref.cpu().numpy(), "y of a replay")
+        assert_parity(k.float().cpu().numpy(), k2.float().cpu().numpy(), "K cache of a replay")
+    assert lay.error() == 0
